@@ -154,10 +154,7 @@ _PM_SEED = 12345
 def prepare(case, seed):
     c = dict(case)
     c["Q"], c["K"], c["V"], c["dO"], c["maps"] = _inputs(case, seed)
-    if c["op"] == "maps":  # a serving loop keeps its workspace
-        c["workspace"] = torch.empty(scram.patchmatch_workspace_bytes(c["S"], c["Hq"], c["Wq"]), dtype=torch.uint8,
-                                     device=_DEVICE)
-    if c["op"] == "backward":
+    if c["op"] == "backward":  # a training loop keeps its workspace
         w = min(w for w in (16, 32, 64, 128) if w >= c["d"])  # the width that the kernels take
         need = scram.sparse_attend_backward_workspace_bytes(c["S"], c["Hq"], c["Wq"], c["Hk"], c["Wk"], c["kappa"], d=w,
                                                             dtype=c["Q"].dtype)
@@ -173,8 +170,7 @@ def run(state):
                              causal=c["causal"])
     if op == "maps":
         if c["kappa"] == 1:
-            return scram.patchmatch(c["Q"], c["K"], c["iters"], _PM_SEED, causal=c["causal"], return_score=True,
-                                    workspace=c["workspace"])
+            return scram.patchmatch(c["Q"], c["K"], c["iters"], _PM_SEED, causal=c["causal"], return_score=True)
         return scram.patchmatch_kappa(c["Q"], c["K"], c["kappa"], c["iters"], _PM_SEED, sep=c["sep"], causal=c["causal"])
     if op == "attend":
         return scram.sparse_attend(c["Q"], c["K"], c["V"], c["maps"], c["window"], causal=c["causal"])
