@@ -21,7 +21,6 @@ struct AttParams {
     int causal;           // drop keys after the query (raster order)
     int Hq, Wq;
     Tiling tq;            // blocks -> tiles of the query grid (set per storage type and width)
-    int rc;               // cluster radius of the tile kernel (Chebyshev, between match centres)
 };
 
 // ---------------------------------------------------------------------------
@@ -217,7 +216,7 @@ __global__ __launch_bounds__(kBlock) void attend_kernel(AttParams p)
 }
 
 // ---------------------------------------------------------------------------
-// K4 on the matrix cores (bf16 storage, windows of side 3, 5 or 7, up to 8
+// K4 on the matrix cores (bf16 storage, windows of side 3, 5, 7 or 9, up to 8
 // maps, with or without the causal mask)
 // ---------------------------------------------------------------------------
 // A wave takes a 4 x 4 tile of queries (16 on an 8 x 8 block tile; 16
@@ -261,18 +260,94 @@ __global__ __launch_bounds__(kBlock) void attend_kernel(AttParams p)
 // second holding back the keys of the first's windows): each
 // window is kept in the box of its own centre's cluster, less the keys of
 // the query's earlier windows (and of those after the query).
-// (at most 96 VGPRs: five waves per SIMD hide more of the row loads than four; the causal mask's
-// registers and those of up to 4 windows do not fit there without spills, so they take four, and
-// up to 8 windows, or 4 with the causal mask, three)
+// One query's row key by key, for lanes (m, 0 .. 3) of a wave: what the lane-group kernels compute.  The matrix-core
+// kernel takes it for a query whose result is not finite, since a non-finite value row of the box reaches every query of the
+// cluster through 0 * inf, also one whose window does not hold it.
+template <int D, int MK>
+__device__ void attend_plain_row(const AttParams& p, uint32_t g, int g4)
+{
+    using TR = TileRow<D>;
+    uint32_t s, rem;
+    divmod(g, p.div_plane, s, rem);
+    const unsigned char* const Kb = static_cast<const unsigned char*>(p.K) + static_cast<size_t>(s) * p.nkeys * (2 * D);
+    const unsigned char* const Vb = static_cast<const unsigned char*>(p.V) + static_cast<size_t>(s) * p.nkeys * (2 * D);
+    constexpr int kE = TR::kPb / 2;  // channels per piece
+    typename TR::Frag q[TR::kDs];
+    float acc[TR::kDs][kE];
+    const unsigned char* const qrow = static_cast<const unsigned char*>(p.Q) + static_cast<size_t>(g) * (2 * D);
+#pragma unroll
+    for (int ds = 0; ds < TR::kDs; ++ds) {
+        q[ds] = TR::frag(qrow, ds, g4);
+#pragma unroll
+        for (int i = 0; i < kE; ++i) acc[ds][i] = 0.f;
+    }
+    const WindowSet<MK> ws = make_window_set<MK>(p, g, rem);
+    float m = -INFINITY, l = 0.f;
+    for (int e = 0; e < p.kappa; ++e) {
+        uint32_t u, v;
+        ws.centre(e, u, v);
+        const int r0 = max(static_cast<int>(u) - p.b, 0), r1 = min(static_cast<int>(u) + p.b, p.Hk - 1);
+        const int c0 = max(static_cast<int>(v) - p.b, 0), c1 = min(static_cast<int>(v) + p.b, p.Wk - 1);
+        for (int r = r0; r <= r1; ++r)
+            for (int c = c0; c <= c1; ++c) {
+                if (ws.skip(e, r, c)) continue;
+                const uint32_t off = static_cast<uint32_t>(r * p.Wk + c) * (2u * D);
+                float sc = 0.f;
+#pragma unroll
+                for (int ds = 0; ds < TR::kDs; ++ds) sc = TR::dot(q[ds], TR::frag(Kb + off, ds, g4), sc);
+                sc += __shfl_xor(sc, 16);
+                sc += __shfl_xor(sc, 32);
+                sc *= p.scale_log2e;
+                const float mb = fmaxf(m, sc);
+                if (mb == -INFINITY) continue;
+                if (mb > m + kRescaleSlack) {
+                    const float alpha = __builtin_amdgcn_exp2f(m - mb);
+                    l *= alpha;
+#pragma unroll
+                    for (int ds = 0; ds < TR::kDs; ++ds)
+#pragma unroll
+                        for (int i = 0; i < kE; ++i) acc[ds][i] *= alpha;
+                    m = mb;
+                }
+                const float pj = __builtin_amdgcn_exp2f(sc - m);
+                l += pj;
+#pragma unroll
+                for (int ds = 0; ds < TR::kDs; ++ds) {
+                    const typename TR::Frag vr = TR::frag(Vb + off, ds, g4);
+#pragma unroll
+                    for (int i = 0; i < kE; ++i) acc[ds][i] = fmaf(pj, static_cast<float>(vr[i]), acc[ds][i]);
+                }
+            }
+    }
+    const float inv = l > 0.f ? 1.f / l : 0.f;
+    uint16_t* const orow = static_cast<uint16_t*>(p.out) + static_cast<size_t>(g) * D;
+#pragma unroll
+    for (int ds = 0; ds < TR::kDs; ++ds)
+#pragma unroll
+        for (int i = 0; i < kE; ++i)
+            orow[32 * ds + kE * g4 + i] = static_cast<uint16_t>(f32_to_bf16_rne(acc[ds][i] * inv));
+}
+
+// Waves per SIMD the registers are sized for: at d = 64 at most 96 VGPRs, five waves, hide more of the row
+// loads than four; the causal mask's registers and those of up to 4 windows do not fit there without spills,
+// so they take four, and up to 8 windows, or 4 with the causal mask, three; 128 channels double the
+// accumulators, the query's operands and the rows in flight.
+constexpr int tile_waves(int D, bool causal, int MK)
+{
+    if (D == 128) return causal || MK > 1 ? 2 : 3;
+    return MK > 4 || (MK == 4 && causal) ? 3 : causal || MK > 1 ? 4 : 5;
+}
+
 template <int D, int W, bool CAUSAL, int MK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(MK > 4 || (MK == 4 && CAUSAL) ? 3 : CAUSAL || MK > 1 ? 4 : 5))) void
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(tile_waves(D, CAUSAL, MK)))) void
 attend_tile_kernel(AttParams p)
 {
+    using TR = TileRow<D>;
     constexpr int B = W / 2;
-    constexpr int kDs = D / 32;        // 32-channel contraction steps of S^T
+    constexpr int rc = tile_radius(W);
+    constexpr int kDs = TR::kDs;       // contraction steps of S^T
     constexpr int kOt = D / 16;        // 16-channel tiles of O^T
     constexpr int kRowB = 2 * D + 16;  // LDS row stride: the 16-byte pad spreads a column read over the banks
-    constexpr int kPer = D / 32;       // 16-byte pieces per lane: a row (D / 8 pieces) is read by 4 consecutive lanes
     constexpr int kWaves = kBlock / 64;
     __shared__ __align__(16) unsigned char s_k[kWaves][16 * kRowB], s_v[kWaves][16 * kRowB];
 
@@ -300,14 +375,13 @@ attend_tile_kernel(AttParams p)
         u = static_cast<int>(uu);
         v = static_cast<int>(vv);
     }
-    // B operand of S^T: query m, channels 32 ds + 8 g4 .. + 7; and the same channels of the match's key
-    bf16x8_t qf[kDs];
-    uint4 kc[kDs];
-    const uint16_t* const qrow = static_cast<const uint16_t*>(p.Q) + static_cast<size_t>(gq) * D;
+    // B operand of S^T: query m, lane group g4's channels; and the same channels of the match's key
+    typename TR::Frag qf[kDs], kc[kDs];
+    const unsigned char* const qrow = static_cast<const unsigned char*>(p.Q) + static_cast<size_t>(gq) * (2 * D);
 #pragma unroll
     for (int ds = 0; ds < kDs; ++ds) {
-        qf[ds] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qrow + 32 * ds + 8 * g4));
-        kc[ds] = *reinterpret_cast<const uint4*>(Kb + centre * (2u * D) + 64u * ds + 16u * g4);
+        qf[ds] = TR::frag(qrow, ds, g4);
+        kc[ds] = TR::frag(Kb + centre * (2u * D), ds, g4);
     }
 
     // ---- clusters of the 16 match centres and their key boxes ----
@@ -337,7 +411,7 @@ attend_tile_kernel(AttParams p)
             int iu = u, iv = v;
 #pragma unroll
             for (int e = 0; e < NW; ++e) iu = ew == e ? ju[e] : iu, iv = ew == e ? jv[e] : iv;
-            tc = tile_clusters_joint<B, NJ>(valid && ew < p.kappa, iu, iv, lane, p.rc, p.Hk, p.Wk);
+            tc = tile_clusters_joint<B, NJ>(valid && ew < p.kappa, iu, iv, lane, rc, p.Hk, p.Wk);
 #pragma unroll
             for (int e = 0; e < NJ; ++e) jmine[e] = __shfl(tc.mine, m + 16 * e);
         }
@@ -355,7 +429,7 @@ attend_tile_kernel(AttParams p)
         }
         joint_round(0);
     } else {
-        tc = tile_clusters<B, CAUSAL>(valid, u, v, m, lane, p.rc, p.Hk, p.Wk, qx, qy);
+        tc = tile_clusters<B, CAUSAL>(valid, u, v, m, lane, rc, p.Hk, p.Wk, qx, qy);
     }
     if (tc.nclu == 0) return;  // no query of this wave lies inside the grid
     int nclu = tc.nclu, mine = tc.mine, wr0 = tc.wr0, wrn = tc.wrn;
@@ -399,13 +473,7 @@ attend_tile_kernel(AttParams p)
     // other clusters.
     float s_centre = 0.f;
 #pragma unroll
-    for (int ds = 0; ds < kDs; ++ds) {
-        const uint4 qa = __builtin_bit_cast(uint4, qf[ds]);
-        s_centre = dot2_bf16(qa.x, kc[ds].x, s_centre);
-        s_centre = dot2_bf16(qa.y, kc[ds].y, s_centre);
-        s_centre = dot2_bf16(qa.z, kc[ds].z, s_centre);
-        s_centre = dot2_bf16(qa.w, kc[ds].w, s_centre);
-    }
+    for (int ds = 0; ds < kDs; ++ds) s_centre = TR::dot(qf[ds], kc[ds], s_centre);
     s_centre += __shfl_xor(s_centre, 16);
     s_centre += __shfl_xor(s_centre, 32);
     float mref = s_centre * sl2e, nref = -mref;
@@ -419,8 +487,7 @@ attend_tile_kernel(AttParams p)
     // products.  Block k of a cluster holds raster slots 16 k .. 16 k + 15 of its box; its 16 key rows and
     // 16 value rows are read a row per 4 consecutive lanes, staged in this wave's LDS tile and read back in
     // the products' operand layout.
-    const int lslot = lane >> 2, lpiece = lane & 3;  // every lane: one key slot, 16-byte pieces lpiece (+ 4)
-    static_assert(kPer == 1 || kPer == 2, "32 or 64 channels");
+    const int lslot = lane >> 2, lpiece = lane & 3;  // every lane: one key slot, pieces lpiece (+ 4 ...)
     unsigned char* const tk = s_k[wave];
     unsigned char* const tv = s_v[wave];
     // A operand of O^T for tile o, read with the transposing LDS load: in each 16-lane group the load
@@ -431,25 +498,17 @@ attend_tile_kernel(AttParams p)
     using Box = TileBox;
     auto box_of = [&](int cl) { return tile_box(tc, cl, p.Wk); };
 
-    uint4 kr0, kr1, vr0, vr1;  // this lane's pieces of the rows in flight
+    RowPieces<D> kr, vr;  // this lane's pieces of the rows in flight
     // a slot past the box's last row (weight 0) reads the box's last row, which the block holds anyway
     auto load = [&](uint32_t key, uint32_t klast) {
-        const uint32_t off = min(key, klast) * (2u * D) + 16u * lpiece;
-        kr0 = *reinterpret_cast<const uint4*>(Kb + off);
-        vr0 = *reinterpret_cast<const uint4*>(Vb + off);
-        if constexpr (kPer == 2) {
-            kr1 = *reinterpret_cast<const uint4*>(Kb + off + 64);
-            vr1 = *reinterpret_cast<const uint4*>(Vb + off + 64);
-        }
+        const uint32_t off = min(key, klast) * (2u * D) + static_cast<uint32_t>(TR::kPb) * lpiece;
+        kr.load(Kb, off);
+        vr.load(Vb, off);
     };
     auto stage = [&]() {
-        const int off = lslot * kRowB + 16 * lpiece;
-        *reinterpret_cast<uint4*>(tk + off) = kr0;
-        *reinterpret_cast<uint4*>(tv + off) = vr0;
-        if constexpr (kPer == 2) {
-            *reinterpret_cast<uint4*>(tk + off + 64) = kr1;
-            *reinterpret_cast<uint4*>(tv + off + 64) = vr1;
-        }
+        const int off = lslot * kRowB + TR::kPb * lpiece;
+        kr.store(tk + off);
+        vr.store(tv + off);
     };
     // this lane's load slot: box column lc and key index lkey (past the box's last row the slots run on
     // into the rows below it, and their keys are clamped to the box's last)
@@ -471,11 +530,7 @@ attend_tile_kernel(AttParams p)
         // S^T of this block: lane holds keys 4 g4 + i (slots 16 k + 4 g4 + i) for query m
         f32x4_t sc = zero;
 #pragma unroll
-        for (int ds = 0; ds < kDs; ++ds) {
-            const bf16x8_t kf = __builtin_bit_cast(
-                bf16x8_t, *reinterpret_cast<const uint4*>(tk + m * kRowB + 16 * (4 * ds + g4)));
-            sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[ds], sc, 0, 0, 0);
-        }
+        for (int ds = 0; ds < kDs; ++ds) sc = TR::product(TR::frag(tk + m * kRowB, ds, g4), qf[ds], sc);
         // which of the 4 slots lie in query m's window (bit i: slot 16 k + 4 g4 + i)
         uint32_t bits;
         if constexpr (JOINT) {
@@ -638,7 +693,7 @@ attend_tile_kernel(AttParams p)
             v = static_cast<int>(vv);
 #pragma unroll
             for (int f = 0; f < kOther; ++f) dw[f] = f < e ? cu[f] - u : 1 << 20;
-            tc = tile_clusters<B, CAUSAL>(valid, u, v, m, lane, p.rc, p.Hk, p.Wk, qx, qy);
+            tc = tile_clusters<B, CAUSAL>(valid, u, v, m, lane, rc, p.Hk, p.Wk, qx, qy);
             nclu = tc.nclu, mine = tc.mine, wr0 = tc.wr0, wrn = tc.wrn;
             wcols = tc.wcols;
             wave_lds_sync();  // the last block's LDS reads come before the next pass's writes
@@ -658,6 +713,15 @@ attend_tile_kernel(AttParams p)
         const uint32_t w1 = bf2(acc[o][2] * inv, acc[o][3] * inv);
         *reinterpret_cast<uint2*>(orow + 16 * o + 4 * g4) = make_uint2(w0, w1);
     }
+    if constexpr (D == 16 || D == 128 || W == 9) {
+        // the shapes whose inputs need not be finite
+        float t = lt;
+#pragma unroll
+        for (int o = 0; o < kOt; ++o) t += (fabsf(acc[o][0]) + fabsf(acc[o][1])) + (fabsf(acc[o][2]) + fabsf(acc[o][3]));
+        const uint64_t bad = __ballot(!(t < INFINITY));
+        const uint32_t of = static_cast<uint32_t>(bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xFFFFu;  // bit m: query m
+        if ((of >> m) & 1u) attend_plain_row<D, MK>(p, g, g4);
+    }
 }
 
 template <typename T, int D, int MK>
@@ -674,15 +738,23 @@ hipError_t run_attend_m(const AttParams& p, int window, uint64_t blocks, hipStre
     }
 }
 
-// The matrix-core kernel takes bf16 storage with 32 or 64 channels, windows
-// of side 3, 5 or 7 (one per map, up to kMaxKappa maps; with or without the
-// causal mask), a positive scale and slices of at most 4 GiB of key rows; the
-// lane-group kernels take every other call.
+// The matrix-core kernel takes bf16 storage, windows of side 3, 5, 7 or 9 (up
+// to four maps, with or without the causal mask; with 32 or 64 channels and
+// windows up to 7 all kMaxKappa), a positive scale and slices of at most 4 GiB
+// of key rows; the lane-group kernels take every other call.  They also keep
+// one 3 x 3 window of 128 channels and all 3 x 3 windows of 16: their boxes
+// hold few rows that queries share (16 maps of 128 x 128: 24.9 us against 34.7
+// with 16 channels, half of them 38.7 against 43.8 with 128).  Measured over
+// the lane-group kernels (256 x 256 x 4 or 128 x 128 x 8 queries, us): 9 x 9
+// 202 -> 88 (64 channels), 63 -> 31 (32); 128 channels 5 x 5 70 -> 53, 7 x 7
+// 120 -> 65, causal 5 x 5 72 -> 49, three 9 x 9 windows 548 -> 127; 16
+// channels (four times the queries) 5 x 5 51 -> 45, 7 x 7 95 -> 61, 9 x 9
+// 150 -> 78.
 #ifndef SCRAM_ATTEND_TILE
 #define SCRAM_ATTEND_TILE 1
 #endif
 template <typename T, int D>
-constexpr bool kTileKernel = SCRAM_ATTEND_TILE && std::is_same<T, uint16_t>::value && (D == 32 || D == 64);
+constexpr bool kTileKernel = SCRAM_ATTEND_TILE && std::is_same<T, uint16_t>::value;
 
 template <typename T, int D>
 hipError_t run_attend(const AttParams& p0, int window, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
@@ -690,13 +762,13 @@ hipError_t run_attend(const AttParams& p0, int window, hipStream_t st, hipEvent_
     constexpr int G = Lanes<T, D>::kAttend;
     AttParams p = p0;
     if constexpr (kTileKernel<T, D>) {
-        if (p.kappa <= kMaxKappa && (window == 3 || window == 5 || window == 7) && p.scale_log2e > 0.f &&
+        constexpr bool kMid = D == 32 || D == 64;
+        const bool fits = kMid && window <= 7 ? p.kappa <= kMaxKappa : p.kappa <= 4;
+        const bool pays = kMid || window > 3 || (D == 128 && p.kappa > 1);
+        const uint64_t tiles = tiling_blocks(make_tiling(p.Hq, p.Wq, kBlock / 4), p.n / (static_cast<uint32_t>(p.Hq) * p.Wq));
+        if (tiles <= kMaxBlocks && fits && pays && window >= 3 && window <= 9 && p.scale_log2e > 0.f &&
             static_cast<uint64_t>(p.nkeys) * (2 * D) <= 0xFFFFFFFFull) {
             p.tq = make_tiling(p.Hq, p.Wq, kBlock / 4);
-            // cluster radius: boxes at most 2 rc + window wide (27 for 7 x 7 windows), so a box's slots stay
-            // below 1024 and its two-row column bit fields below 32 bits; 10 measured faster than 4-8 and 11
-            p.rc = 10;
-            const uint64_t tiles = tiling_blocks(p.tq, p.n / p.tq.plane);
             auto go = [&](auto w) {
                 constexpr int Wn = decltype(w)::value;
                 // the smallest bound on the windows per query that holds this call's
@@ -705,14 +777,17 @@ hipError_t run_attend(const AttParams& p0, int window, hipStream_t st, hipEvent_
                     return p.causal ? launch(attend_tile_kernel<D, Wn, true, MK>, tiles, st, e0, e1, p)
                                     : launch(attend_tile_kernel<D, Wn, false, MK>, tiles, st, e0, e1, p);
                 };
+                if constexpr ((D == 32 || D == 64) && Wn <= 7) {
+                    if (p.kappa > 4) return with(std::integral_constant<int, kMaxKappa>{});
+                }
                 return p.kappa == 1   ? with(std::integral_constant<int, 1>{})
                        : p.kappa == 2 ? with(std::integral_constant<int, 2>{})
-                       : p.kappa <= 4 ? with(std::integral_constant<int, 4>{})
-                                      : with(std::integral_constant<int, kMaxKappa>{});
+                                      : with(std::integral_constant<int, 4>{});
             };
             return window == 3   ? go(std::integral_constant<int, 3>{})
                    : window == 5 ? go(std::integral_constant<int, 5>{})
-                                 : go(std::integral_constant<int, 7>{});
+                   : window == 7 ? go(std::integral_constant<int, 7>{})
+                                 : go(std::integral_constant<int, 9>{});
         }
     }
     p.tq = make_tiling(p.Hq, p.Wq, Row<T, D, G>::kQpb, kLaneSkew);
@@ -762,7 +837,9 @@ uint64_t attend_max_blocks(int dtype, const Grid& g)
         using T = decltype(t);
         constexpr int D = decltype(d)::value;
         const uint64_t lanes = tiling_blocks(make_tiling(g.Hq, g.Wq, Row<T, D, Lanes<T, D>::kAttend>::kQpb, kLaneSkew), g.S);
-        const uint64_t tiles = kTileKernel<T, D> ? tiling_blocks(make_tiling(g.Hq, g.Wq, kBlock / 4), g.S) : 0;
+        // (16 and 128 channels go to the lane-group kernels where the tiles would be too many)
+        constexpr bool kTiles = kTileKernel<T, D> && (D == 32 || D == 64);
+        const uint64_t tiles = kTiles ? tiling_blocks(make_tiling(g.Hq, g.Wq, kBlock / 4), g.S) : 0;
         return lanes > tiles ? lanes : tiles;
     });
 }

@@ -26,6 +26,8 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 // bf16 pair (a in the low half, b in the high half) from the high halves of two fp32 patterns
 __device__ __forceinline__ uint32_t hi16_pair(uint32_t a, uint32_t b)
@@ -73,6 +75,79 @@ __device__ __forceinline__ uint32_t tile_wave_item(const Tiling& tq, int wave, i
 {
     return tq.lw == 3 ? ((4u * (wave >> 1) + (m >> 2)) << 3) + 4u * (wave & 1) + (m & 3) : 16u * wave + m;
 }
+
+// Rows of D bf16 channels as the products' operands: S^T contracts 32 channels a
+// step (lane group g4 holds 8 consecutive ones), or all 16 of narrow rows at
+// once (4 each), and a row is read by 4 consecutive lanes, kPer pieces each.
+template <int D>
+struct TileRow {
+    static constexpr int kDs = D >= 32 ? D / 32 : 1;  // contraction steps
+    using Frag = std::conditional_t<D == 16, bf16x4_t, bf16x8_t>;
+    using Piece = std::conditional_t<D == 16, u32x2_t, u32x4_t>;
+    static constexpr int kPer = D >= 32 ? D / 32 : 1;  // pieces per lane
+    static constexpr int kPb = static_cast<int>(sizeof(Piece));
+
+    static __device__ __forceinline__ Frag frag(const unsigned char* row, int ds, int g4)
+    {
+        return __builtin_bit_cast(Frag, *reinterpret_cast<const Piece*>(row + 64 * ds + kPb * g4));
+    }
+
+    static __device__ __forceinline__ f32x4_t product(Frag a, Frag b, f32x4_t c)
+    {
+        if constexpr (D == 16)
+            return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
+        else
+            return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+
+    // c + a . b over the lane's channels
+    static __device__ __forceinline__ float dot(Frag a, Frag b, float c)
+    {
+        const Piece x = __builtin_bit_cast(Piece, a), y = __builtin_bit_cast(Piece, b);
+        c = dot2_bf16(x.x, y.x, c);
+        c = dot2_bf16(x.y, y.y, c);
+        if constexpr (D != 16) {
+            c = dot2_bf16(x.z, y.z, c);
+            c = dot2_bf16(x.w, y.w, c);
+        }
+        return c;
+    }
+};
+
+// A lane's pieces of one key or value row in flight.  (Named members: an array
+// loaded on two paths of a loop ends in scratch memory.)
+template <int D>
+struct RowPieces {
+    using TR = TileRow<D>;
+    using Piece = typename TR::Piece;
+    Piece a, b, c, d;
+
+    // pieces at `off` bytes of the rows, 64 bytes apart
+    __device__ __forceinline__ void load(const unsigned char* rows, uint32_t off)
+    {
+        a = *reinterpret_cast<const Piece*>(rows + off);
+        if constexpr (TR::kPer > 1) b = *reinterpret_cast<const Piece*>(rows + off + 64);
+        if constexpr (TR::kPer > 2) {
+            c = *reinterpret_cast<const Piece*>(rows + off + 128);
+            d = *reinterpret_cast<const Piece*>(rows + off + 192);
+        }
+    }
+
+    __device__ __forceinline__ void store(unsigned char* to) const
+    {
+        *reinterpret_cast<Piece*>(to) = a;
+        if constexpr (TR::kPer > 1) *reinterpret_cast<Piece*>(to + 64) = b;
+        if constexpr (TR::kPer > 2) {
+            *reinterpret_cast<Piece*>(to + 128) = c;
+            *reinterpret_cast<Piece*>(to + 192) = d;
+        }
+    }
+};
+
+// Cluster radius (Chebyshev, between match centres) for windows of side W: boxes at most 2 rc + W <= 27 wide,
+// so a box's slots stay below 1024 and its two-row column bit fields below 32 bits; 10 measured faster than
+// 4-8 and 11 for windows up to 7.
+constexpr int tile_radius(int W) { return W <= 7 ? 10 : (27 - W) / 2; }
 
 // A wave's clusters.  Cluster c's box (rows r0 .. r0 + h - 1, columns
 // c0 .. c0 + bw - 1, nb blocks of 16 raster slots, a 16-slot step of q16 rows

@@ -1,0 +1,59 @@
+"""The matrix-core attend at 16 and 128 channels and with 9 x 9 windows, against the oracle (``-m gpu``)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import scram_inputs.synth as synth
+from gpu_util import TOL, row_rel_err, tile_maps, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# 16 channels take the matrix cores from 5 x 5 on, 128 from 5 x 5 on or with several maps, 32 and 64 with 9 x 9 windows
+SHAPES = [(16, 5), (16, 7), (16, 9), (32, 9), (64, 9), (128, 3), (128, 5), (128, 9)]
+# several tiles with ragged edges, the smallest grids, one row, one column, two grids
+GRIDS = [(2, 21, 37, 21, 37), (1, 3, 5, 3, 5), (1, 1, 50, 1, 50), (1, 50, 1, 50, 1), (1, 19, 11, 33, 30)]
+
+
+@pytest.mark.parametrize("d,window", SHAPES)
+@pytest.mark.parametrize("grid", GRIDS, ids=lambda g: "x".join(map(str, g)))
+def test_attend_widths(scram, d, window, grid):
+    S, Hq, Wq, Hk, Wk = grid
+    rng = np.random.default_rng(d + window + Hq)
+    Q, K, V = (synth._round_bf16(rng.standard_normal(s).astype(np.float32)) for s in
+               ((S, Hq, Wq, d), (S, Hk, Wk, d), (S, Hk, Wk, d)))
+    Qd, Kd, Vd = (to_dev(x, "bf16") for x in (Q, K, V))
+    m = tile_maps(S, Hq, Wq, Hk, Wk, rng)
+    sets = [m[n][None] for n in ("random", "coherent", "lattice7", "lattice10", "two_far", "outliers")]
+    sets += [np.stack([m["coherent"], m["outliers"]]), np.stack([m["random"], m["coherent"], m["corner_last"]])]
+    for J in sets:
+        for causal in ((False, True) if (Hq, Wq) == (Hk, Wk) else (False,)):
+            got = scram.sparse_attend(Qd, Kd, Vd, torch.from_numpy(J).cuda(), window, causal=causal)
+            ref = oracle.sparse_attend(Q, K, V, J, window, d ** -0.5, flags=oracle.CAUSAL if causal else 0)
+            err = row_rel_err(got.double().cpu().numpy(), ref)
+            assert err.max() <= TOL["bf16"], (J.shape[0], causal, err.max())
+            empty = ~np.any(ref, axis=-1)
+            assert not got.cpu()[torch.from_numpy(empty)].any()  # a query without keys: a zero row
+
+
+@pytest.mark.parametrize("d,window", SHAPES)
+def test_non_finite_values_stay_in_their_windows(scram, d, window):
+    """A value row with an infinity or a NaN reaches exactly the queries whose windows hold its key, although
+    the rows are read in blocks that neighbouring queries share."""
+    S, H, W, b = 1, 24, 24, window // 2
+    rng = np.random.default_rng(d + window)
+    Q, K, V = (synth._round_bf16(rng.standard_normal((S, H, W, d)).astype(np.float32)) for _ in range(3))
+    J = np.stack([np.arange(H * W).reshape(S, H, W), rng.integers(0, H * W, (S, H, W))]).astype(np.int32)
+    clean = scram.sparse_attend(*(to_dev(x, "bf16") for x in (Q, K, V)), torch.from_numpy(J).cuda(), window)
+    bad = [(7, 9), (20, 3)]
+    V[0, 7, 9, d // 2] = np.inf
+    V[0, 20, 3, 1] = np.nan
+    got = scram.sparse_attend(*(to_dev(x, "bf16") for x in (Q, K, V)), torch.from_numpy(J).cuda(), window)
+    near = np.zeros((S, H, W), bool)
+    for u, v in bad:
+        for m in J:
+            near |= (np.abs(m // W - u) <= b) & (np.abs(m % W - v) <= b)
+    got, clean = got.float().cpu().numpy(), clean.float().cpu().numpy()
+    assert np.isfinite(got[~near]).all()
+    np.testing.assert_allclose(got[~near], clean[~near], rtol=2 ** -7, atol=1e-3)  # (bf16 rounding of either path)
+    assert (~np.isfinite(got[near])).any(axis=-1).all()
