@@ -1021,6 +1021,389 @@ bwd_key_strip_kernel(BwdParams p)
 }
 
 // ---------------------------------------------------------------------------
+// Key side on the matrix cores, fp32 storage.  The strips, their entries and
+// the key-set tests are those of the bf16 kernel above; the products are the
+// fp32 ones (16x16x4), so nothing is split or rounded on the way.  Per chunk
+// of 16 entries (lane (m, g4) = (lane mod 16, lane div 16)):
+//   S^T = Q_E K_w^T, dP^T = dO_E V_w^T    lane group g4 contracts the channels
+//       g4 D / 4 .. (D / 4 + 1) g4 - 1, so that a lane's channels are
+//       consecutive in memory and LDS; lane: entries 4 g4 + i, key m
+//   dV_w += P dO_E, dK_w += dS Q_E        step i contracts the entries
+//       4 g4 + i: register i of the first products is the operand; column m of
+//       channel tile o stands for channel m D / 16 + o, so a lane reads and
+//       stores consecutive channels
+// A chunk's rows load while the previous chunk is in the matrix cores, the
+// entry codes a chunk before that.  Bound by the latency of that chain at two
+// waves per SIMD (64 channels; three below): 32 x 64 x 64 keys, 3 x 3: 67 us
+// against 117 for the lane-group kernels, which copied the rows into entry
+// order first (the products alone would take 19).
+// ---------------------------------------------------------------------------
+constexpr int kStripFE = 16;  // entries per chunk
+
+// The rows of gradients of key (kx, ky), entry by entry, by one wave: what the
+// lane-group kernels compute.  The strip kernel takes it for the keys whose
+// results are not finite, since a non-finite entry row reaches every key of
+// the strip through 0 * inf, also one whose neighbourhood does not hold it.
+template <int D>
+__device__ void key_grads_plain(const BwdParams& p, uint32_t s, int kx, int ky, int lane)
+{
+    constexpr int kC = D > 64 ? 2 : 1;  // channels lane (and lane + 64) of the row
+    const bool on = lane < D;
+    const size_t kg = static_cast<size_t>(s) * p.nkeys + static_cast<size_t>(kx) * p.Wk + ky;
+    const float* const Qf = static_cast<const float*>(p.Q);
+    const float* const Gf = static_cast<const float*>(p.dO);
+    float kv[kC], vv[kC], dk[kC], dv[kC];
+#pragma unroll
+    for (int c = 0; c < kC; ++c) {
+        kv[c] = on ? static_cast<const float*>(p.K)[kg * D + lane + 64 * c] : 0.f;
+        vv[c] = on ? static_cast<const float*>(p.V)[kg * D + lane + 64 * c] : 0.f;
+        dk[c] = dv[c] = 0.f;
+    }
+    const int32_t* const off = p.offsets + static_cast<size_t>(s) * p.nkeys;
+    const int c0 = max(ky - p.b, 0), c1 = min(ky + p.b, p.Wk - 1);
+    for (int r = max(kx - p.b, 0); r <= min(kx + p.b, p.Hk - 1); ++r)
+        for (int x = off[r * p.Wk + c0]; x < off[r * p.Wk + c1 + 1]; ++x) {
+            uint32_t e, g, sl, rem;
+            divmod(static_cast<uint32_t>(p.entries[x]), p.div_n, e, g);
+            divmod(g, p.div_plane, sl, rem);
+            bool ok = !p.causal || static_cast<uint32_t>(kx) * p.Wk + ky <= rem;
+            for (int f = 0; f < static_cast<int>(e) && ok; ++f) {
+                uint32_t fu, fv;
+                divmod(static_cast<uint32_t>(clamp_index(p.J[static_cast<size_t>(f) * p.n + g], p.nkeys)), p.div_wk,
+                       fu, fv);
+                ok = abs(static_cast<int>(fu) - kx) > p.b || abs(static_cast<int>(fv) - ky) > p.b;
+            }
+            if (!ok) continue;
+            float q[kC], go[kC], sc = 0.f, dp = 0.f;
+#pragma unroll
+            for (int c = 0; c < kC; ++c) {
+                q[c] = on ? Qf[static_cast<size_t>(g) * D + lane + 64 * c] : 0.f;
+                go[c] = on ? Gf[static_cast<size_t>(g) * D + lane + 64 * c] : 0.f;
+                sc = fmaf(q[c], kv[c], sc);
+                dp = fmaf(go[c], vv[c], dp);
+            }
+#pragma unroll
+            for (int m = 1; m < 64; m <<= 1) {
+                sc += __shfl_xor(sc, m);
+                dp += __shfl_xor(dp, m);
+            }
+            const float pr = __builtin_amdgcn_exp2f(sc * p.scale_log2e - p.lse2[g]);
+            const float ds = pr * (dp - p.Dq[g]);
+#pragma unroll
+            for (int c = 0; c < kC; ++c) {
+                dk[c] = fmaf(ds, q[c], dk[c]);
+                dv[c] = fmaf(pr, go[c], dv[c]);
+            }
+        }
+    if (on)
+#pragma unroll
+        for (int c = 0; c < kC; ++c) {
+            p.dK[kg * D + lane + 64 * c] = dk[c] * p.scale;
+            p.dV[kg * D + lane + 64 * c] = dv[c];
+        }
+}
+
+template <int N>
+__device__ __forceinline__ void load_floats(float (&v)[N], const float* a)
+{
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int i = 0; i < N; i += 4) {
+            const f32x4_t x = *reinterpret_cast<const f32x4_t*>(a + i);
+            v[i] = x[0], v[i + 1] = x[1], v[i + 2] = x[2], v[i + 3] = x[3];
+        }
+    } else if constexpr (N == 2) {
+        const f32x2_t x = *reinterpret_cast<const f32x2_t*>(a);
+        v[0] = x[0], v[1] = x[1];
+    } else {
+        v[0] = a[0];
+    }
+}
+
+template <int N>
+__device__ __forceinline__ void store_floats(float* a, const float (&v)[N])
+{
+    if constexpr (N >= 4) {
+#pragma unroll
+        for (int i = 0; i < N; i += 4) *reinterpret_cast<f32x4_t*>(a + i) = f32x4_t{v[i], v[i + 1], v[i + 2], v[i + 3]};
+    } else if constexpr (N == 2) {
+        *reinterpret_cast<f32x2_t*>(a) = f32x2_t{v[0], v[1]};
+    } else {
+        a[0] = v[0];
+    }
+}
+
+// The products of 16 rows in LDS (this lane's row a) with 16 keys (this lane's key b) over 4 N channels, N of
+// them here: sums of 8 channels in the matrix cores, added pairwise, as deep as the lane-group kernels' sums.
+template <int N>
+__device__ __forceinline__ f32x4_t strip_dots(const float* a, const float* b)
+{
+    if constexpr (N == 4) {
+        const f32x4_t x = *reinterpret_cast<const f32x4_t*>(a);
+        f32x4_t t = f32x4_t{0.f, 0.f, 0.f, 0.f}, u = t;
+        t = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0], b[0], t, 0, 0, 0);
+        u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[2], b[2], u, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1], b[1], t, 0, 0, 0);
+        u = __builtin_amdgcn_mfma_f32_16x16x4f32(x[3], b[3], u, 0, 0, 0);
+        return t + u;
+    } else {
+        return strip_dots<N / 2>(a, b) + strip_dots<N / 2>(a + N / 2, b + N / 2);
+    }
+}
+
+template <int D, int MODE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(D >= 64 ? 2 : 3))) void
+bwd_key_strip_f32_kernel(BwdParams p)
+{
+    constexpr bool MULTI = MODE == kStripMulti;
+    constexpr bool kQueryIndex = MODE != kStripPlain;
+    constexpr int kCE = kStripFE;
+    constexpr int kRowF = D + 4;   // row stride in LDS, floats (padded)
+    constexpr int kCh = D / 4;     // contraction steps of the first products: channels per lane group
+    constexpr int kOt = D / 16;    // channel tiles of the second
+    constexpr int kLR = D / 4;     // lanes per staged row
+    constexpr int kRpi = 64 / kLR; // rows per load instruction
+    constexpr int kRep = kCE / kRpi;
+    constexpr bool kAhead = D <= 64;  // the next chunk's rows in registers during the products
+    __shared__ __align__(16) float s_q[kCE * kRowF], s_g[kCE * kRowF];
+    __shared__ int4 s_meta[kCE];  // match row, match column, lse2 bits, D bits
+    __shared__ int32_t s_el[kQueryIndex ? kCE : 1][2];  // as in the bf16 kernel
+    __shared__ int32_t s_lo[kStripMaxRows], s_pre[kStripMaxRows + 1];
+
+    const int lane = threadIdx.x & 63;
+    const int m = lane & 15, g4 = lane >> 4;
+    const uint32_t blk = xcd_remap(blockIdx.x, gridDim.x);
+
+    // the strip, as in the bf16 kernel
+    uint32_t s, k, tr, tc;
+    divmod(blk / kStripWaves, p.tk.div_slice, s, k);
+    tile_coords(p.tk, k, tr, tc);
+    const int tw = 1 << p.tk.lw, th = kTileKeys >> p.tk.lw;
+    const int x0 = static_cast<int>(tr) * th, y0 = static_cast<int>(tc) * tw;
+    const int w4 = static_cast<int>(blk % kStripWaves);
+    const bool quad = p.tk.lw == 3 && th == 8;
+    const int it0 = 16 * w4;
+    const int sr0 = quad ? x0 + 4 * (w4 >> 1) : x0 + (it0 >> p.tk.lw);
+    const int sr1 = quad ? sr0 + 3 : x0 + ((it0 + 15) >> p.tk.lw);
+    const int sc0 = quad ? y0 + 4 * (w4 & 1) : y0 + (it0 & (tw - 1));
+    const int sc1 = quad ? sc0 + 3 : sc0 + min(tw, 16) - 1;
+    auto strip_key = [&](int i, int& x, int& y) {
+        x = quad ? sr0 + (i >> 2) : x0 + ((it0 + i) >> p.tk.lw);
+        y = quad ? sc0 + (i & 3) : y0 + ((it0 + i) & (tw - 1));
+    };
+    const int sC = sc1 - sc0 + 1, sR = 16 / sC;
+    auto strip_bits = [&](int rlo, int rhi, int clo, int chi) {
+        rlo = max(rlo, 0), rhi = min(rhi, sR - 1), clo = max(clo, 0), chi = min(chi, sC - 1);
+        uint32_t bits = 0u;
+        if (clo <= chi) {
+            const uint32_t cb = ((2u << chi) - 1u) & ~((1u << clo) - 1u);
+            for (int r = rlo; r <= rhi; ++r) bits |= cb << (sC * r);
+        }
+        return bits;
+    };
+    if (sr0 >= p.Hk || sc0 >= p.Wk) return;  // the strip lies past the grid's edge
+    const int hr0 = max(sr0 - p.b, 0), hr1 = min(sr1 + p.b, p.Hk - 1);
+    const int hc0 = max(sc0 - p.b, 0), hc1 = min(sc1 + p.b, p.Wk - 1);
+    const int nrows = hr1 - hr0 + 1;  // at most kStripMaxRows
+    const int32_t* const off = p.offsets + static_cast<size_t>(s) * p.nkeys;
+    int E;
+    {
+        int cnt = 0;
+        if (lane < nrows) {
+            const int r = hr0 + lane;
+            const int32_t lo = off[r * p.Wk + hc0];
+            s_lo[lane] = lo;
+            cnt = off[r * p.Wk + hc1 + 1] - lo;
+        }
+        int incl = cnt;
+#pragma unroll
+        for (int k2 = 1; k2 < 64; k2 <<= 1) {
+            const int y = __shfl_up(incl, k2, 64);
+            if (lane >= k2) incl += y;
+        }
+        if (lane < nrows) s_pre[lane + 1] = incl;
+        if (lane == 0) s_pre[0] = 0;
+        E = __shfl(incl, nrows - 1, 64);
+    }
+    wave_lds_sync();
+
+    // this lane's key (column of the first products): key m of the strip
+    int kx, ky;
+    strip_key(m, kx, ky);
+    const bool key_ok = kx < p.Hk && ky < p.Wk;
+    const size_t kslice = static_cast<size_t>(s) * p.nkeys;
+    const size_t krow = kslice + (key_ok ? static_cast<size_t>(kx) * p.Wk + ky : static_cast<size_t>(sr0) * p.Wk + sc0);
+    float kf[kCh], vf[kCh];
+    load_floats<kCh>(kf, static_cast<const float*>(p.K) + krow * D + g4 * kCh);
+    load_floats<kCh>(vf, static_cast<const float*>(p.V) + krow * D + g4 * kCh);
+    const uint32_t key_local = static_cast<uint32_t>(kx) * p.Wk + ky;  // raster index (causal test)
+
+    const f32x4_t zero = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    f32x4_t dk[kOt], dv[kOt];
+#pragma unroll
+    for (int o = 0; o < kOt; ++o) dk[o] = dv[o] = zero;
+
+    // lane l < 16 finds entry slot l of a chunk
+    auto slot_code = [&](int c0) {
+        const int v = c0 + m;
+        if (v >= E) return -1;
+        int lo = 0, hi = nrows - 1;  // halo row holding flat position v: the last with pre <= v
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_pre[mid] <= v) lo = mid; else hi = mid - 1;
+        }
+        return static_cast<int>(p.entries[s_lo[lo] + (v - s_pre[lo])]);
+    };
+    const int er = lane / kLR, ep = lane % kLR;
+    f32x4_t rq[kRep], rg[kRep];  // this lane's pieces of the next chunk's rows
+    int32_t match = -1;
+    float lse = 0.f, dq = 0.f;
+    uint32_t qe = 0u, qg = 0u;
+    int code = -1;
+    // the rows and statistics of the chunk whose codes are in `code`
+    auto fetch = [&]() {
+        if (code >= 0) divmod(static_cast<uint32_t>(code), p.div_n, qe, qg);
+        match = -1;
+        if (code >= 0 && g4 == 0) {
+            match = p.J[code];
+            lse = p.lse2[qg];
+            dq = p.Dq[qg];
+        }
+        const int my_q = code >= 0 ? static_cast<int>(qg) : -1;
+#pragma unroll
+        for (int j = 0; j < kRep; ++j) {
+            // (past the entries a zero row keeps the operands finite)
+            const int qj = __shfl(my_q, er + kRpi * j, 64);
+            const size_t at = static_cast<size_t>(max(qj, 0)) * D + 4 * ep;
+            rq[j] = rg[j] = zero;
+            if (qj >= 0) {
+                rq[j] = *reinterpret_cast<const f32x4_t*>(static_cast<const float*>(p.Q) + at);
+                rg[j] = *reinterpret_cast<const f32x4_t*>(static_cast<const float*>(p.dO) + at);
+            }
+        }
+    };
+    code = slot_code(0);
+    if constexpr (kAhead) fetch();
+    int next = slot_code(kCE);
+    for (int c0 = 0; c0 < E; c0 += kCE) {
+        if constexpr (!kAhead) fetch();
+#pragma unroll
+        for (int j = 0; j < kRep; ++j) {
+            *reinterpret_cast<f32x4_t*>(s_q + (er + kRpi * j) * kRowF + 4 * ep) = rq[j];
+            *reinterpret_cast<f32x4_t*>(s_g + (er + kRpi * j) * kRowF + 4 * ep) = rg[j];
+        }
+        if (g4 == 0) {
+            int4 meta = make_int4(-(1 << 30), -(1 << 30), 0, 0);  // no key is near this match
+            if constexpr (kQueryIndex) s_el[m][0] = s_el[m][1] = 0;
+            if (code >= 0) {
+                uint32_t mu, mv;
+                divmod(static_cast<uint32_t>(clamp_index(match, p.nkeys)), p.div_wk, mu, mv);
+                meta = make_int4(static_cast<int>(mu), static_cast<int>(mv), __float_as_int(lse), __float_as_int(dq));
+                if constexpr (kQueryIndex) {
+                    uint32_t sl, local;
+                    divmod(qg, p.div_plane, sl, local);
+                    s_el[m][1] = static_cast<int32_t>(local);
+                }
+                if constexpr (MULTI) {
+                    int32_t pc[kMaxKappa - 1];
+#pragma unroll
+                    for (int f = 0; f < kMaxKappa - 1; ++f)
+                        pc[f] = f < static_cast<int>(qe) ? p.J[static_cast<size_t>(f) * p.n + qg] : 0;
+                    uint32_t held = 0u;
+#pragma unroll
+                    for (int f = 0; f < kMaxKappa - 1; ++f) {
+                        if (f < static_cast<int>(qe)) {
+                            uint32_t fu, fv;
+                            divmod(static_cast<uint32_t>(clamp_index(pc[f], p.nkeys)), p.div_wk, fu, fv);
+                            const int ru = static_cast<int>(fu) - sr0, cv = static_cast<int>(fv) - sc0;
+                            held |= strip_bits(ru - p.b, ru + p.b, cv - p.b, cv + p.b);
+                        }
+                    }
+                    s_el[m][0] = static_cast<int32_t>(held);
+                }
+            }
+            s_meta[m] = meta;
+        }
+        code = next;
+        if (kAhead && c0 + kCE < E) fetch();
+        next = slot_code(c0 + 2 * kCE);
+        wave_lds_sync();
+
+        // S^T, dP^T of the chunk's entries against the strip's keys
+        const f32x4_t sc = strip_dots<kCh>(s_q + m * kRowF + g4 * kCh, kf);
+        const f32x4_t dp = strip_dots<kCh>(s_g + m * kRowF + g4 * kCh, vf);
+        // P and dS of (key m, entry 4 g4 + i)
+        float pr[4], ds[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int te = 4 * g4 + i;
+            const int4 mt = s_meta[te];
+            bool ok = key_ok && abs(mt.x - kx) <= p.b && abs(mt.y - ky) <= p.b;
+            if constexpr (MULTI) {
+                ok = ok && !((static_cast<uint32_t>(s_el[te][0]) >> m) & 1u);
+                if (p.causal) ok = ok && key_local <= static_cast<uint32_t>(s_el[te][1]);
+            } else if constexpr (MODE == kStripCausal) {
+                ok = ok && key_local <= static_cast<uint32_t>(s_el[te][1]);
+            }
+            pr[i] = ok ? __builtin_amdgcn_exp2f(sc[i] * p.scale_log2e - __int_as_float(mt.z)) : 0.f;
+            ds[i] = ok ? pr[i] * (dp[i] - __int_as_float(mt.w)) : 0.f;
+        }
+        // dV_w += P dO_E, dK_w += dS Q_E, two channel tiles at a time: the chunk's sums first, then onto the
+        // strip's (sums of sums round less than one long sum)
+        constexpr int kOh = kOt < 2 ? 1 : 2;
+#pragma unroll
+        for (int oh = 0; oh < kOt; oh += kOh) {
+            f32x4_t ck[kOh], cv[kOh];
+#pragma unroll
+            for (int o = 0; o < kOh; ++o) ck[o] = cv[o] = zero;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                float bq[kOh], bg[kOh];
+                load_floats<kOh>(bq, s_q + (4 * g4 + i) * kRowF + m * kOt + oh);
+                load_floats<kOh>(bg, s_g + (4 * g4 + i) * kRowF + m * kOt + oh);
+#pragma unroll
+                for (int o = 0; o < kOh; ++o) {
+                    cv[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(pr[i], bg[o], cv[o], 0, 0, 0);
+                    ck[o] = __builtin_amdgcn_mfma_f32_16x16x4f32(ds[i], bq[o], ck[o], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int o = 0; o < kOh; ++o) {
+                dk[oh + o] += ck[o];
+                dv[oh + o] += cv[o];
+            }
+        }
+        wave_lds_sync();  // this chunk's LDS reads come before the next chunk's writes
+    }
+
+    // lane holds keys 4 g4 + r of the strip, channels m D / 16 + o
+    bool finite = true;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        int ox, oy;
+        strip_key(4 * g4 + r, ox, oy);
+        if (ox >= p.Hk || oy >= p.Wk) continue;
+        const size_t row = (kslice + static_cast<size_t>(ox) * p.Wk + oy) * D + m * kOt;
+        float ok[kOt], ov[kOt];
+#pragma unroll
+        for (int o = 0; o < kOt; ++o) {
+            finite = finite && fabsf(dk[o][r]) < INFINITY && fabsf(dv[o][r]) < INFINITY;
+            ok[o] = dk[o][r] * p.scale;
+            ov[o] = dv[o][r];
+        }
+        store_floats<kOt>(p.dK + row, ok);
+        store_floats<kOt>(p.dV + row, ov);
+    }
+    if (__any(!finite)) {
+        for (int i = 0; i < 16; ++i) {
+            int ox, oy;
+            strip_key(i, ox, oy);
+            if (ox < p.Hk && oy < p.Wk) key_grads_plain<D>(p, s, ox, oy, lane);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Query side on the matrix cores (bf16 storage, d 32 or 64, windows 3/5/7,
 // up to MK maps, with or without the causal mask; several maps as in the
 // attend's matrix-core kernel: one pass over the joint clusters of up to four
@@ -1518,13 +1901,23 @@ hipError_t run_backward(const BwdParams& p0, hipStream_t st, hipEvent_t* ev, Inv
                         : query(std::integral_constant<int, 0>{});
     if (e != hipSuccess) return e;
     if ((e = inverse()) != hipSuccess) return e;
-    if constexpr (std::is_same<T, uint16_t>::value) {
-        // key side on the matrix cores; a one-key window (b = 0) stays on the lane-group kernels, whose dp
-        // is the query kernel's own arithmetic, so that dS = p (dp - D) is exactly 0 there
-        if (p.b >= 1 && p.b <= kTileMaxB) {
-            BwdParams pt = p;
-            pt.tk = make_tiling(p.Hk, p.Wk, kTileKeys);
-            const uint64_t tblocks = kStripWaves * tiling_blocks(pt.tk, p.keys_total / p.nkeys);
+    // key side on the matrix cores; a one-key window (b = 0, or fp32 and a one-key grid) stays on the
+    // lane-group kernels, whose dp is the query kernel's own arithmetic, so that dS = p (dp - D) is exactly
+    // 0 there
+    // (fp32 rows of 128 channels, whose fragments and sums overfill the registers, pay there only with several
+    // large windows: two maps, 7 x 7, 8 x 128 x 128: 2521 -> 1887 us; 3 x 3 569 -> 704)
+    constexpr bool kWideF32 = std::is_same<T, float>::value && D == 128;
+    const bool one_key = p.b == 0 || (std::is_same<T, float>::value && p.nkeys == 1);
+    if (!one_key && p.b <= kTileMaxB && !(kWideF32 && (p.kappa == 1 || p.b < 3))) {
+        BwdParams pt = p;
+        pt.tk = make_tiling(p.Hk, p.Wk, kTileKeys);
+        const uint64_t tblocks = kStripWaves * tiling_blocks(pt.tk, p.keys_total / p.nkeys);
+        if constexpr (std::is_same<T, float>::value) {
+            if (p.kappa > 1) return launch_wave(bwd_key_strip_f32_kernel<D, kStripMulti>, tblocks, st, k0, k1, pt);
+            if constexpr (D < 128)
+                return p.causal ? launch_wave(bwd_key_strip_f32_kernel<D, kStripCausal>, tblocks, st, k0, k1, pt)
+                                : launch_wave(bwd_key_strip_f32_kernel<D, kStripPlain>, tblocks, st, k0, k1, pt);
+        } else {
             return p.kappa > 1 ? launch_wave(bwd_key_strip_kernel<D, kStripMulti>, tblocks, st, k0, k1, pt)
                    : p.causal  ? launch_wave(bwd_key_strip_kernel<D, kStripCausal>, tblocks, st, k0, k1, pt)
                                : launch_wave(bwd_key_strip_kernel<D, kStripPlain>, tblocks, st, k0, k1, pt);

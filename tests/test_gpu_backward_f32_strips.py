@@ -1,0 +1,57 @@
+"""The fp32 key side of the backward on the matrix cores, against the oracle (``-m gpu``)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import tile_maps, to_dev
+
+pytestmark = pytest.mark.gpu
+
+# square 8 x 8 key tiles with ragged edges, 64 x 1 and 4 x 16 ones, the smallest grids, two grids
+GRIDS = [(2, 21, 13, 21, 13), (1, 70, 1, 70, 1), (2, 5, 70, 3, 67), (1, 3, 5, 3, 5), (1, 9, 31, 30, 22)]
+# 128 channels take the strips with several maps and windows from 7 x 7 on; 17 is past them
+WIDTHS = [(16, 3), (16, 9), (32, 5), (64, 3), (64, 15), (64, 17), (128, 3), (128, 7)]
+
+
+@pytest.mark.parametrize("d,window", WIDTHS)
+@pytest.mark.parametrize("grid", GRIDS, ids=lambda g: "x".join(map(str, g)))
+def test_f32_key_strips(scram, d, window, grid):
+    S, Hq, Wq, Hk, Wk = grid
+    rng = np.random.default_rng(d + 7 * window + Hq)
+    Q, dO = (rng.standard_normal((S, Hq, Wq, d)).astype(np.float32) for _ in range(2))
+    K, V = (rng.standard_normal((S, Hk, Wk, d)).astype(np.float32) for _ in range(2))
+    dev = [to_dev(x, "f32") for x in (Q, K, V)]
+    m = tile_maps(S, Hq, Wq, Hk, Wk, rng)
+    # one map; entries of one key beyond a chunk (constant); two and three maps, repeated and distant
+    sets = [m[n][None] for n in ("random", "coherent", "constant", "two_far")]
+    sets += [np.stack([m["coherent"], m["outliers"]]), np.stack([m["coherent"], m["coherent"], m["random"]])]
+    for J in sets:
+        for causal in ((False, True) if (Hq, Wq) == (Hk, Wk) else (False,)):
+            got = scram.sparse_attend_backward(*dev, torch.from_numpy(J).cuda(), to_dev(dO, "f32"), window, causal=causal)
+            ref = oracle.sparse_attend_backward(Q, K, V, J, window, d ** -0.5, dO, flags=oracle.CAUSAL if causal else 0)
+            for name, g, r in zip(("dQ", "dK", "dV"), got, ref):
+                err = np.abs(g.double().cpu().numpy() - r).max() / max(np.abs(r).max(), 1e-30)
+                assert err <= 2e-5, (name, J.shape[0], causal, err)  # the bar of the other backward tests
+
+
+@pytest.mark.parametrize("d", [16, 64])
+def test_non_finite_gradients_stay_with_their_keys(scram, d):
+    """A query whose output gradient holds an infinity or a NaN reaches exactly the keys of its windows,
+    although the key side reads entries in chunks that the keys of a strip share."""
+    S, H, W, window = 1, 24, 24, 3
+    rng = np.random.default_rng(d)
+    Q, K, V, dO = (to_dev(rng.standard_normal((S, H, W, d)).astype(np.float32), "f32") for _ in range(4))
+    J = torch.arange(H * W, dtype=torch.int32, device="cuda").reshape(S, H, W)
+    clean = scram.sparse_attend_backward(Q, K, V, J, dO, window)
+    dO[0, 5, 6, 3] = float("inf")
+    dO[0, 17, 20, 1] = float("nan")
+    got = scram.sparse_attend_backward(Q, K, V, J, dO, window)
+    near = torch.zeros(S, H, W, dtype=torch.bool, device="cuda")
+    for u, v in ((5, 6), (17, 20)):
+        near[0, u - 1:u + 2, v - 1:v + 2] = True
+    for g, c in zip(got[1:], clean[1:]):
+        assert torch.isfinite(g[~near]).all()
+        # the same sums in either order of the entries
+        assert torch.allclose(g[~near], c[~near], rtol=1e-5, atol=2e-5 * float(c.abs().max()))
+        assert (~torch.isfinite(g[near])).any(dim=-1).all()
