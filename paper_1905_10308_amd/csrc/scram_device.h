@@ -246,6 +246,25 @@ __device__ __forceinline__ void load_row(const T* base, uint32_t row, int lane, 
     for (int c = 0; c < Row<T, D, G>::kCh; ++c) v[c] = p[c * G];
 }
 
+// The same with 32-bit byte offsets from a wave-uniform base (rows below 4 GiB
+// in all): the loads take the base from scalar registers, and a row's address
+// costs one shift instead of 64-bit arithmetic.
+template <typename T, int D, int G>
+__device__ __forceinline__ void load_row32(const void* base, uint32_t row, int lane, uint4 (&v)[Row<T, D, G>::kCh])
+{
+    const uint32_t off = row * static_cast<uint32_t>(Row<T, D, G>::kBytes) + 16u * lane;
+#pragma unroll
+    for (int c = 0; c < Row<T, D, G>::kCh; ++c)
+        v[c] = *reinterpret_cast<const uint4*>(static_cast<const char*>(base) + (off + 16u * G * c));
+}
+
+// Leave v as it is, whatever it holds (no instruction): for registers that
+// some lanes do not load and do not use.
+__device__ __forceinline__ void any_value(uint4& v)
+{
+    asm volatile("" : "=v"(v.x), "=v"(v.y), "=v"(v.z), "=v"(v.w));
+}
+
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c)
@@ -313,10 +332,11 @@ __device__ __forceinline__ float row_score(const uint4 (&q)[Row<T, D, G>::kCh], 
     return group_sum<G>(lane_dot<T, Row<T, D, G>::kCh>(q, k));
 }
 
-// Higher score wins; equal scores go to the lower flat key index.
+// Higher score wins; equal scores go to the lower flat key index.  (No short
+// circuit: a branch per comparison costs more than the comparison.)
 __device__ __forceinline__ bool better(float s, int32_t i, float bs, int32_t bi)
 {
-    return s > bs || (s == bs && i < bi);
+    return (s > bs) | ((s == bs) & (i < bi));
 }
 
 __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f)

@@ -125,13 +125,23 @@ __global__ __launch_bounds__(kBlock) void pm_init_kernel(PmParams p)
 //      queries).
 // Because "better" is a strict total order, visiting the candidates of
 // stage 1 in any order gives the same result as the order of Algorithm 1.
+//
+// Instruction issue and the load path are both close to full (VALU 63 %,
+// TD 73 % on 4 x 256 x 256 queries of 64 bf16 channels), so what is left out
+// here counts: 32-bit row offsets from a scalar base, comparisons without
+// branches, no zeroing of the registers a masked load leaves, the neighbours'
+// matches loaded together, and a step's random words fetched a step ahead.
+// These took the 7 sweeps from 303 to 289 us, 8 x 111 x 97 causal queries of
+// 32 channels with two runs from 146 to 132 us.  Batches (kNb) of 4, 6 and 9
+// rows: 290, 311 and 330 us against 289 with 3.
 // ---------------------------------------------------------------------------
 // NP < 0: no validity test (a single-match run without masking); NP >= 0:
 // causal masking and/or up to NP previous runs.  FIRST: the first sweep of a
 // run started from the random initial field, which is not read from memory:
 // each query recomputes its own initial match and those of its neighbours
 // (initial_draw) and scores its own.
-template <typename T, int D, int G, int QPG, int kNb, bool PROP, bool RS, int NP, bool FIRST = false>
+// OFF32: a slice's rows lie below 4 GiB, so a row is a 32-bit offset.
+template <typename T, int D, int G, int QPG, int kNb, bool PROP, bool RS, int NP, bool FIRST, bool OFF32>
 __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
 {
     constexpr bool VALID = NP >= 0;
@@ -152,6 +162,12 @@ __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
     uint32_t g[QPG], s[QPG], x[QPG], y[QPG];
     bool live[QPG];
     const T* Ks[QPG];
+    auto load_key = [&](int j, uint32_t row, uint4 (&v)[CH]) {
+        if constexpr (OFF32)
+            load_row32<T, D, G>(Ks[j], row, lane, v);
+        else
+            load_row<T, D, G>(Ks[j], row, lane, v);
+    };
     uint4 q[QPG][CH];
     int32_t cur[QPG], cur0[QPG];
     float best[QPG];
@@ -165,6 +181,7 @@ __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
         uint32_t rem;
         divmod(g[j], p.div_plane, s[j], rem);
         divmod(rem, p.div_wq, x[j], y[j]);
+        s[j] = __builtin_amdgcn_readfirstlane(s[j]);  // a tile lies in one slice
         Ks[j] = static_cast<const T*>(p.K) + static_cast<size_t>(s[j]) * p.nkeys * D;
         load_row<T, D, G>(static_cast<const T*>(p.Q), g[j], lane, q[j]);
         if constexpr (FIRST) {
@@ -180,7 +197,7 @@ __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
     uint4 kinc[QPG][CH];
     if constexpr (FIRST) {
 #pragma unroll
-        for (int j = 0; j < QPG; ++j) load_row<T, D, G>(Ks[j], cur[j], lane, kinc[j]);
+        for (int j = 0; j < QPG; ++j) load_key(j, cur[j], kinc[j]);
     }
     // validity variant: the previous runs' matches of each query; an invalid
     // incumbent counts as minus infinity
@@ -226,40 +243,57 @@ __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
     for (int j = 0; j < QPG; ++j) {
         count[j] = 0;
         int32_t* list = s_list + (j * kGroups + qslot) * kList;
+        // candidate slot i < 16: jump index i/4 over 8,4,2,1; direction i%4 over row-1, row+1, col-1, col+1
+        auto offset = [&](int i, int& ox, int& oy) {
+            const int jump = 8 >> (i >> 2);
+            const int dir = i & 3;
+            ox = dir == 0 ? -jump : (dir == 1 ? jump : 0);
+            oy = dir == 2 ? -jump : (dir == 3 ? jump : 0);
+        };
+        // the neighbours' matches, all loads in flight together (a neighbour outside the grid reads the
+        // query's own entry, which its slot then leaves out)
+        constexpr int kProp = 16 / G;
+        int32_t near[kProp];
+        bool inside[kProp];
+        if constexpr (PROP) {
+            const uint32_t slice0 = g[j] - (x[j] * p.Wq + y[j]);
+#pragma unroll
+            for (int m = 0; m < kProp; ++m) {
+                int ox, oy;
+                offset(lane + m * G, ox, oy);
+                const int nx = static_cast<int>(x[j]) + ox, ny = static_cast<int>(y[j]) + oy;
+                inside[m] = (nx >= 0) & (nx < p.Hq) & (ny >= 0) & (ny < p.Wq);
+                const uint32_t nrem = inside[m] ? static_cast<uint32_t>(nx * p.Wq + ny) : x[j] * p.Wq + y[j];
+                if constexpr (FIRST)
+                    near[m] = initial_draw(p, slice0 + nrem, nrem);
+                else
+                    near[m] = Jp[slice0 + nrem];
+            }
+        }
 #pragma unroll
         for (int m = 0; m < kSlots; ++m) {
             const int i = lane + m * G;
             int32_t c = -1;
-            if (PROP && i < 16) {
-                // jump index i/4 over 8,4,2,1; direction i%4 over row-1, row+1,
-                // col-1, col+1: the neighbour's match shifted back by the offset
-                const int jump = 8 >> (i >> 2);
-                const int dir = i & 3;
-                const int ox = dir == 0 ? -jump : (dir == 1 ? jump : 0);
-                const int oy = dir == 2 ? -jump : (dir == 3 ? jump : 0);
-                const int nx = static_cast<int>(x[j]) + ox, ny = static_cast<int>(y[j]) + oy;
-                if (nx >= 0 && nx < p.Hq && ny >= 0 && ny < p.Wq) {
-                    const uint32_t ng = static_cast<uint32_t>((static_cast<size_t>(s[j]) * p.Hq + nx) * p.Wq + ny);
-                    uint32_t nb;
-                    bool seen = false;  // scored by this query in the previous sweep
-                    if constexpr (FIRST) {
-                        nb = static_cast<uint32_t>(initial_draw(p, ng, static_cast<uint32_t>(nx * p.Wq + ny)));
-                    } else {
-                        int32_t raw = Jp[ng];
-                        if (p.marked_in) {
-                            seen = (static_cast<uint32_t>(raw) & kStable) != 0u;
-                            raw = static_cast<int32_t>(raw & ~kStable);
-                        }
-                        nb = clamp_index(raw, p.nkeys);
-                    }
-                    uint32_t nu, nv;
-                    divmod(nb, p.div_wk, nu, nv);
-                    const int r = static_cast<int>(nu) - ox, cc = static_cast<int>(nv) - oy;
-                    if (!seen && r >= 0 && r < p.Hk && cc >= 0 && cc < p.Wk) {
-                        c = r * p.Wk + cc;
-                        if (VALID && !val[j].ok(r, cc, c)) c = -1;
+            if (PROP && m < kProp) {
+                // the neighbour's match shifted back by the offset
+                int ox, oy;
+                offset(i, ox, oy);
+                int32_t raw = near[m];
+                bool use = inside[m];
+                if constexpr (!FIRST) {
+                    if (p.marked_in) {
+                        use = use & (raw >= 0);  // a marked one was scored by this query in the previous sweep
+                        raw = static_cast<int32_t>(raw & ~kStable);
                     }
                 }
+                const uint32_t nb = clamp_index(raw, p.nkeys);
+                uint32_t nu, nv;
+                divmod(nb, p.div_wk, nu, nv);
+                const int r = static_cast<int>(nu) - ox, cc = static_cast<int>(nv) - oy;
+                use = use & (r >= 0) & (r < p.Hk) & (cc >= 0) & (cc < p.Wk);
+                const int32_t key = static_cast<int32_t>(nb) - (ox * p.Wk + oy);
+                if constexpr (VALID) use = use && val[j].ok(r, cc, key);
+                c = use ? key : -1;
             } else if (RS && i == 16) {
                 // random-search step 0: uniform over the whole key grid
                 const uint32_t r = __umulhi(w0[j].x, static_cast<uint32_t>(p.Hk));
@@ -298,7 +332,7 @@ __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
 #pragma unroll
             for (int e = 0; e < kNb; ++e)
 #pragma unroll
-                for (int c = 0; c < CH; ++c) raw[j][e][c] = make_uint4(0u, 0u, 0u, 0u);
+                for (int c = 0; c < CH; ++c) any_value(raw[j][e][c]);
         int most = count[0];
 #pragma unroll
         for (int j = 1; j < QPG; ++j) most = max(most, count[j]);
@@ -312,7 +346,7 @@ __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
                     const int kk = k0 + e;
                     const int32_t entry = list[min(kk, kList - 1)];  // in bounds; stale past the end
                     idx[j][e] = kk < count[j] ? entry : cur0[j];
-                    if (kk < count[j]) load_row<T, D, G>(Ks[j], idx[j][e], lane, raw[j][e]);
+                    if (kk < count[j]) load_key(j, idx[j][e], raw[j][e]);
                 }
             }
             float sc[QPG][kNb];
@@ -344,34 +378,46 @@ __global__ __launch_bounds__(kBlock) void pm_iter_kernel(PmParams p)
             divmod(static_cast<uint32_t>(cur[j]), p.div_wk, cu[j], cv[j]);
             w[j] = w0[j];
         }
-        for (int k = 1; k < p.rs_steps; ++k) {
-            const int m = k >> 1;
-            if ((k & 1) == 0 && m % G == 0) {
+        // step k's words, from the lane of the group that holds their block
+        uint32_t wr[QPG], wc[QPG];
+        auto words = [&](int k) {
+            const int src = gbase + (k >> 1) % G;
 #pragma unroll
-                for (int j = 0; j < QPG; ++j) {
-                    w[j] = make_uint4(0u, 0u, 0u, 0u);
-                    if (m + lane < nblk)
-                        w[j] = philox4x32_10(g[j], p.t, static_cast<uint32_t>(m + lane),
-                                             static_cast<uint32_t>(p.n_prev), p.key0, p.key1);
-                }
+            for (int j = 0; j < QPG; ++j) {
+                wr[j] = __shfl((k & 1) ? w[j].z : w[j].x, src);
+                wc[j] = __shfl((k & 1) ? w[j].w : w[j].y, src);
             }
-            const int src = gbase + m % G;
+        };
+        words(1);
+        for (int k = 1; k < p.rs_steps; ++k) {
             const int dk = p.R >> k;
             int32_t idx[QPG];
             uint32_t rr[QPG], rc[QPG];
             uint4 kr[QPG][CH];
 #pragma unroll
             for (int j = 0; j < QPG; ++j) {
-                const uint32_t wr = __shfl((k & 1) ? w[j].z : w[j].x, src);
-                const uint32_t wc = __shfl((k & 1) ? w[j].w : w[j].y, src);
                 const int lo_r = max(static_cast<int>(cu[j]) - dk, 0);
                 const int hi_r = min(static_cast<int>(cu[j]) + dk, p.Hk - 1);
                 const int lo_c = max(static_cast<int>(cv[j]) - dk, 0);
                 const int hi_c = min(static_cast<int>(cv[j]) + dk, p.Wk - 1);
-                rr[j] = lo_r + __umulhi(wr, static_cast<uint32_t>(hi_r - lo_r + 1));
-                rc[j] = lo_c + __umulhi(wc, static_cast<uint32_t>(hi_c - lo_c + 1));
+                rr[j] = lo_r + __umulhi(wr[j], static_cast<uint32_t>(hi_r - lo_r + 1));
+                rc[j] = lo_c + __umulhi(wc[j], static_cast<uint32_t>(hi_c - lo_c + 1));
                 idx[j] = static_cast<int32_t>(rr[j] * p.Wk + rc[j]);
-                load_row<T, D, G>(Ks[j], idx[j], lane, kr[j]);
+                load_key(j, idx[j], kr[j]);
+            }
+            // the next step's words while the rows load
+            if (k + 1 < p.rs_steps) {
+                const int m = (k + 1) >> 1;
+                if ((k & 1) != 0 && m % G == 0) {
+#pragma unroll
+                    for (int j = 0; j < QPG; ++j) {
+                        w[j] = make_uint4(0u, 0u, 0u, 0u);
+                        if (m + lane < nblk)
+                            w[j] = philox4x32_10(g[j], p.t, static_cast<uint32_t>(m + lane),
+                                                 static_cast<uint32_t>(p.n_prev), p.key0, p.key1);
+                    }
+                }
+                words(k + 1);
             }
 #pragma unroll
             for (int j = 0; j < QPG; ++j) {
@@ -444,11 +490,19 @@ hipError_t run_iter_v(const PmParams& p, uint32_t flags, uint64_t blocks, hipStr
     constexpr int NB = SCRAM_PM_BATCH;
     const bool prop = !(flags & SCRAM_PM_NO_PROPAGATION);
     const bool rs = !(flags & SCRAM_PM_NO_RANDOM_SEARCH);
-    if (p.first) return launch(pm_iter_kernel<T, D, G, QPG, NB, true, true, NP, true>, blocks, st, e0, e1, p);
-    if (prop && rs) return launch(pm_iter_kernel<T, D, G, QPG, NB, true, true, NP>, blocks, st, e0, e1, p);
-    if (prop) return launch(pm_iter_kernel<T, D, G, QPG, NB, true, false, NP>, blocks, st, e0, e1, p);
-    if (rs) return launch(pm_iter_kernel<T, D, G, QPG, NB, false, true, NP>, blocks, st, e0, e1, p);
-    return launch(pm_iter_kernel<T, D, G, QPG, NB, false, false, NP>, blocks, st, e0, e1, p);
+    if (prop && rs) {
+        // (a slice of at most 4 GiB of key rows: 32-bit offsets)
+        const bool near = static_cast<uint64_t>(p.nkeys) * Row<T, D, G>::kBytes <= 0xFFFFFFFFull;
+        auto go = [&](auto first, auto off32) {
+            return launch(pm_iter_kernel<T, D, G, QPG, NB, true, true, NP, decltype(first)::value, decltype(off32)::value>,
+                          blocks, st, e0, e1, p);
+        };
+        return p.first ? (near ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{}))
+                       : (near ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{}));
+    }
+    if (prop) return launch(pm_iter_kernel<T, D, G, QPG, NB, true, false, NP, false, false>, blocks, st, e0, e1, p);
+    if (rs) return launch(pm_iter_kernel<T, D, G, QPG, NB, false, true, NP, false, false>, blocks, st, e0, e1, p);
+    return launch(pm_iter_kernel<T, D, G, QPG, NB, false, false, NP, false, false>, blocks, st, e0, e1, p);
 }
 
 template <typename T, int D>
