@@ -344,6 +344,19 @@ int scram_snis_attend(const void* Q, const void* K, const void* V, int dtype, co
                       uint64_t seed, uint32_t flags, void* out, float* ess_out, float* var_out, hipEvent_t* events,
                       hipStream_t stream);
 
+/*
+ * Rows of another channel count than the kernels take: `count` (1 to 4) tensors
+ * in one launch.  With unpad == 0 dst[i] (rows[i] rows of `width` elements)
+ * gets the widths[i] elements of each row of src[i] and zeros after them; with
+ * unpad != 0 dst[i] (rows of widths[i] elements) gets the first widths[i] of
+ * each row of src[i] (rows of `width` elements).  1 <= widths[i] <= width;
+ * width 16, 32, 64 or 128; elem_bytes 2 or 4; rows[i] >= 1 and
+ * rows[i] * width < 2^40.  The side `width` wide is 16-byte aligned, the other
+ * one elem_bytes; src[i] and dst[i] do not overlap.  Returns a status code.
+ */
+int scram_pad_channels(int count, const void* const* src, void* const* dst, const int64_t* rows, const int* widths,
+                       int width, int elem_bytes, int unpad, hipStream_t stream);
+
 /* Static, NUL-terminated description of a status code. */
 const char* scram_status_string(int status);
 

@@ -82,6 +82,8 @@ def load(path: str) -> ctypes.CDLL:
     L.scram_snis_attend.argtypes = [P, P, P, I, P, I, I, I, I, I, I, I, I, I, ctypes.c_float, I, ctypes.c_float,
                                     U64, U32, P, P, P, P, P]
     L.scram_snis_attend.restype = I
+    L.scram_pad_channels.argtypes = [I, P, P, P, P, I, I, I, P]
+    L.scram_pad_channels.restype = I
     L.scram_status_string.argtypes = [I]
     L.scram_status_string.restype = ctypes.c_char_p
     L.scram_abi_version.argtypes = []
@@ -100,10 +102,16 @@ def patchmatch_workspace_bytes(S: int, Hq: int, Wq: int) -> int:
 # --------------------------------------------------------------------------
 # torch marshalling
 # --------------------------------------------------------------------------
-def _torch():
-    import torch
+_torch_module = None
 
-    return torch
+
+def _torch():
+    global _torch_module
+    if _torch_module is None:
+        import torch
+
+        _torch_module = torch
+    return _torch_module
 
 
 def _dtype_code_of(dtype) -> int:
@@ -130,8 +138,9 @@ def _dev_tensor(t, name, ndim=None):
 
 
 def _same_device(device, **tensors):
+    index = device.index
     for name, t in tensors.items():
-        if t is not None and t.device != device:
+        if t is not None and t.get_device() != index:
             raise ValueError(f"{name} is on {t.device}, expected {device}")
 
 
@@ -154,20 +163,7 @@ def _workspace(ws, need, device):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
-
-
-def _unpad_into(res, width: int, out=None):
-    """The first ``width`` channels of ``res``, in ``out`` when given (else a new contiguous tensor)."""
-    if res.shape[-1] == width:
-        if out is not None and out is not res:
-            out.copy_(res)
-            return out
-        return res
-    if out is not None:
-        out.copy_(res[..., :width])
-        return out
-    return res[..., :width].contiguous()
+    return None if t is None else t.data_ptr()
 
 
 def _native_width(c: int) -> int:
@@ -179,25 +175,72 @@ def _native_width(c: int) -> int:
     return c
 
 
-def _pad_channels(t, width: int):
-    """``t`` with its last dimension zero-padded to ``width`` (``t`` itself when it already has it).
+def _resize_channels(src, dst, widths, width: int, unpad: bool):
+    """``scram_pad_channels`` on the tensors ``src`` -> ``dst`` (same storage type; one side ``width`` wide,
+    the other ``widths[i]``)."""
+    n = len(src)
+    rows = [t.numel() // t.shape[-1] for t in src]
+    args = (n, (ctypes.c_void_p * n)(*(t.data_ptr() for t in src)), (ctypes.c_void_p * n)(*(t.data_ptr() for t in dst)),
+            (ctypes.c_int64 * n)(*rows), (ctypes.c_int * n)(*widths), width, src[0].element_size(), int(unpad))
+    _call(lib().scram_pad_channels, "scram_pad_channels", src[0].device, args)
+
+
+def _pad_channels(width: int, *tensors):
+    """The tensors with their last dimension zero-padded to ``width`` (those that have it as they are), in
+    one launch.
 
     Zero channels add exact zeros to every dot product, so scores, weights and outputs in the original
     channels are unchanged; the softmax scale is taken from the original width."""
-    if t.shape[-1] == width:
-        return t
-    out = t.new_zeros(tuple(t.shape[:-1]) + (width,))
-    out[..., : t.shape[-1]] = t
+    short = [t for t in tensors if t.shape[-1] < width and t.numel()]
+    if not short or width not in NATIVE_WIDTHS:  # (a width the library rejects)
+        return tensors
+    padded = [t.new_empty(tuple(t.shape[:-1]) + (width,)) for t in short]
+    _resize_channels(short, padded, [t.shape[-1] for t in short], width, False)
+    found = iter(padded)
+    return tuple(next(found) if t.shape[-1] < width and t.numel() else t for t in tensors)
+
+
+def _unpad_into(res, width: int, out=None):
+    """The first ``width`` channels of ``res``, in ``out`` when given (else a new contiguous tensor)."""
+    if res.shape[-1] == width:
+        if out is not None and out is not res:
+            out.copy_(res)
+            return out
+        return res
+    if out is None:
+        out = res.new_empty(tuple(res.shape[:-1]) + (width,))
+    _resize_channels([res], [out], [width], res.shape[-1], True)
     return out
 
 
-def _on(device):
-    """Make ``device`` current for the call: the library launches on the current device."""
-    return _torch().cuda.device(device)
+def _unpad(width: int, *pairs):
+    """For each (tensor of ``width`` channels, n): its first n channels, in one launch."""
+    short = [(t, n) for t, n in pairs if n < width]
+    cut = [t.new_empty(tuple(t.shape[:-1]) + (n,)) for t, n in short]
+    if short:
+        _resize_channels([t for t, _ in short], cut, [n for _, n in short], width, True)
+    found = iter(cut)
+    return tuple(next(found) if n < width else t for t, n in pairs)
 
 
-def _stream(device):
-    return ctypes.c_void_p(_torch().cuda.current_stream(device).cuda_stream)
+def _raw_stream(device):
+    """Handle of the current stream of ``device``."""
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # (a Stream object costs a microsecond more)
+    return raw(device.index) if raw is not None else torch.cuda.current_stream(device).cuda_stream
+
+
+def _call(fn, where: str, device, args):
+    """``fn(*args, stream)`` with ``device`` current (the library launches on the current device) and its
+    current stream; raises if the status is not zero."""
+    torch = _torch()
+    if torch.cuda.current_device() == device.index:
+        rc = fn(*args, _raw_stream(device))
+    else:
+        with torch.cuda.device(device):
+            rc = fn(*args, _raw_stream(device))
+    if rc != 0:
+        raise ScramError(rc, where)
 
 
 def _event_array(events, n):
@@ -246,9 +289,8 @@ def patchmatch_noalloc(Q, K, iters: int, seed: int, *, init=None, init_score=Non
                        None, return_score, events)
 
 
-def _patchmatch(noalloc, Q, K, iters, seed, init, init_score, t0, flags, prev, sep, causal, out, score_out,
-                workspace, return_score, events):
-    torch = _torch()
+def _check_search(Q, K):
+    """Q and K of a search: (S, Hq, Wq, Hk, Wk, d)."""
     _dev_tensor(Q, "Q", 4)
     _dev_tensor(K, "K", 4)
     if K.dtype != Q.dtype:
@@ -257,9 +299,16 @@ def _patchmatch(noalloc, Q, K, iters, seed, init, init_score, t0, flags, prev, s
     Sk, Hk, Wk, dk = K.shape
     if Sk != S or dk != d:
         raise ValueError(f"Q {tuple(Q.shape)} and K {tuple(K.shape)} disagree on slices or channels")
+    _same_device(Q.device, K=K)
+    return S, Hq, Wq, Hk, Wk, d
+
+
+def _patchmatch(noalloc, Q, K, iters, seed, init, init_score, t0, flags, prev, sep, causal, out, score_out,
+                workspace, return_score, events):
+    torch = _torch()
+    S, Hq, Wq, Hk, Wk, d = _check_search(Q, K)
     dev = Q.device
-    _same_device(dev, K=K, init=init, init_score=init_score, prev=prev, out=out, score_out=score_out,
-                 workspace=workspace)
+    _same_device(dev, init=init, init_score=init_score, prev=prev, out=out, score_out=score_out, workspace=workspace)
     if out is None:
         out = torch.empty((S, Hq, Wq), dtype=torch.int32, device=dev)
     if return_score and score_out is None:
@@ -281,23 +330,17 @@ def _patchmatch(noalloc, Q, K, iters, seed, init, init_score, t0, flags, prev, s
     if causal:
         flags |= CAUSAL
     d = _native_width(d)
-    Q, K = _pad_channels(Q, d), _pad_channels(K, d)
+    Q, K = _pad_channels(d, Q, K)
     ev = None if events is None else _event_array(events, 2 * (int(iters) + 1))
-    args = (_ptr(Q), _ptr(K), _dtype_code(Q), S, Hq, Wq, Hk, Wk, d, int(iters),
-            ctypes.c_uint64(int(seed) & 0xFFFFFFFFFFFFFFFF), _ptr(init), _ptr(init_score), int(t0), int(flags),
-            _ptr(prev), int(n_prev), int(sep), _ptr(out), _ptr(score_out))
+    args = (_ptr(Q), _ptr(K), _dtype_code(Q), S, Hq, Wq, Hk, Wk, d, int(iters), int(seed) & 0xFFFFFFFFFFFFFFFF,
+            _ptr(init), _ptr(init_score), int(t0), int(flags), _ptr(prev), int(n_prev), int(sep), _ptr(out),
+            _ptr(score_out))
     if noalloc:
-        with _on(dev):
-            rc = lib().scram_patchmatch_noalloc(*args, ev, _stream(dev))
-        if rc != 0:
-            raise ScramError(rc, "scram_patchmatch_noalloc")
+        _call(lib().scram_patchmatch_noalloc, "scram_patchmatch_noalloc", dev, (*args, ev))
     else:
         workspace = _workspace(workspace, patchmatch_workspace_bytes(S, Hq, Wq), dev)
-        with _on(dev):
-            rc = lib().scram_patchmatch(*args, _ptr(workspace), workspace.numel() * workspace.element_size(), ev,
-                                        _stream(dev))
-        if rc != 0:
-            raise ScramError(rc, "scram_patchmatch")
+        _call(lib().scram_patchmatch, "scram_patchmatch", dev,
+              (*args, _ptr(workspace), workspace.numel() * workspace.element_size(), ev))
     return (out, score_out) if return_score else out
 
 
@@ -332,15 +375,12 @@ def sparse_attend(Q, K, V, argmax, window: int, scale: float | None = None, *, c
     if out is not None:
         _check_buffer(out, "out", (S, Hq, Wq, dv), Q.dtype)
     w = _native_width(max(d, dv))
-    Q, K, V = (_pad_channels(t, w) for t in (Q, K, V))
+    Q, K, V = _pad_channels(w, Q, K, V)
     res = out if out is not None and w == dv else torch.empty((S, Hq, Wq, w), dtype=Q.dtype, device=dev)
     ev = None if events is None else _event_array(events, 2)
-    with _on(dev):
-        rc = lib().scram_sparse_attend(_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(argmax), int(kappa), S, Hq,
-                                       Wq, Hk, Wk, w, w, int(window), float(scale), CAUSAL if causal else 0,
-                                       _ptr(res), ev, _stream(dev))
-    if rc != 0:
-        raise ScramError(rc, "scram_sparse_attend")
+    _call(lib().scram_sparse_attend, "scram_sparse_attend", dev,
+          (_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(argmax), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(window),
+           float(scale), CAUSAL if causal else 0, _ptr(res), ev))
     return _unpad_into(res, dv, out)
 
 
@@ -373,25 +413,19 @@ def sparse_attend_backward(Q, K, V, argmax, dO, window: int, scale: float | None
         scale = d ** -0.5
     dev = Q.device
     _same_device(dev, K=K, V=V, argmax=argmax, dO=dO, workspace=workspace)
-    dQ = torch.empty((S, Hq, Wq, d), dtype=torch.float32, device=dev)
-    dK = torch.empty((S, Hk, Wk, d), dtype=torch.float32, device=dev)
-    dV = torch.empty((S, Hk, Wk, dv), dtype=torch.float32, device=dev)
     w = _native_width(max(d, dv))
-    Q, K, V, dO = (_pad_channels(t, w) for t in (Q, K, V, dO))
-    if w != d or w != dv:
-        dQ, dK, dV = (torch.empty(tuple(t.shape[:-1]) + (w,), dtype=torch.float32, device=dev) for t in (dQ, dK, dV))
+    dQ = torch.empty((S, Hq, Wq, w), dtype=torch.float32, device=dev)
+    dK = torch.empty((S, Hk, Wk, w), dtype=torch.float32, device=dev)
+    dV = torch.empty((S, Hk, Wk, w), dtype=torch.float32, device=dev)
+    Q, K, V, dO = _pad_channels(w, Q, K, V, dO)
     need = sparse_attend_backward_workspace_bytes(S, Hq, Wq, Hk, Wk, kappa, d=w, dtype=Q.dtype)
     workspace = _workspace(workspace, need, dev)
     ev = None if events is None else _event_array(events, 6)
-    with _on(dev):
-        rc = lib().scram_sparse_attend_backward(_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(argmax), int(kappa),
-                                                S, Hq, Wq, Hk, Wk, w, w, int(window), float(scale),
-                                                CAUSAL if causal else 0, _ptr(dO), _ptr(dQ), _ptr(dK), _ptr(dV),
-                                                _ptr(workspace), workspace.numel() * workspace.element_size(), ev,
-                                                _stream(dev))
-    if rc != 0:
-        raise ScramError(rc, "scram_sparse_attend_backward")
-    return _unpad_into(dQ, d), _unpad_into(dK, d), _unpad_into(dV, dv)
+    _call(lib().scram_sparse_attend_backward, "scram_sparse_attend_backward", dev,
+          (_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(argmax), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(window),
+           float(scale), CAUSAL if causal else 0, _ptr(dO), _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(workspace),
+           workspace.numel() * workspace.element_size(), ev))
+    return _unpad(w, (dQ, d), (dK, d), (dV, dv))
 
 
 def sparse_attend_backward_workspace_bytes(S: int, Hq: int, Wq: int, Hk: int, Wk: int, kappa: int = 1, *,
@@ -432,18 +466,15 @@ def snis_attend(Q, K, V, modes, samples: int, *, alpha: float = 0.9, radius: int
     if out is not None:
         _check_buffer(out, "out", (S, Hq, Wq, dv), Q.dtype)
     w = _native_width(max(d, dv))
-    Q, K, V = (_pad_channels(t, w) for t in (Q, K, V))
+    Q, K, V = _pad_channels(w, Q, K, V)
     res = out if out is not None and w == dv else torch.empty((S, Hq, Wq, w), dtype=Q.dtype, device=dev)
     ess_t = torch.empty((S, Hq, Wq), dtype=torch.float32, device=dev) if ess else None
     var_t = torch.empty((S, Hq, Wq, w), dtype=torch.float32, device=dev) if var else None
     ev = None if events is None else _event_array(events, 2)
-    with _on(dev):
-        rc = lib().scram_snis_attend(_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(modes), int(kappa), S, Hq, Wq,
-                                     Hk, Wk, w, w, int(samples), float(alpha), int(radius), float(scale),
-                                     ctypes.c_uint64(int(seed) & 0xFFFFFFFFFFFFFFFF), CAUSAL if causal else 0,
-                                     _ptr(res), _ptr(ess_t), _ptr(var_t), ev, _stream(dev))
-    if rc != 0:
-        raise ScramError(rc, "scram_snis_attend")
+    _call(lib().scram_snis_attend, "scram_snis_attend", dev,
+          (_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(modes), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(samples),
+           float(alpha), int(radius), float(scale), int(seed) & 0xFFFFFFFFFFFFFFFF, CAUSAL if causal else 0, _ptr(res),
+           _ptr(ess_t), _ptr(var_t), ev))
     out = _unpad_into(res, dv, out)
     if var_t is not None:
         var_t = _unpad_into(var_t, dv)
@@ -456,19 +487,39 @@ def patchmatch_kappa(Q, K, kappa: int, iters: int, seed: int, *, sep: int = 1, c
     Run c receives the maps of runs 0..c-1 (Algorithm 2's first step).
     """
     torch = _torch()
-    S, Hq, Wq, _ = Q.shape
     if not 1 <= kappa <= MAX_KAPPA:
         raise ValueError(f"kappa must be in [1, {MAX_KAPPA}]")
-    maps = torch.empty((kappa, S, Hq, Wq), dtype=torch.int32, device=Q.device)
-    ws = torch.empty(patchmatch_workspace_bytes(S, Hq, Wq), dtype=torch.uint8, device=Q.device)
-    for c in range(kappa):
-        patchmatch(Q, K, iters, seed, flags=flags, prev=maps[:c] if c else None, sep=sep, causal=causal,
-                   out=maps[c], workspace=ws)
+    S, Hq, Wq, Hk, Wk, d = _check_search(Q, K)
+    dev = Q.device
+    maps = torch.empty((kappa, S, Hq, Wq), dtype=torch.int32, device=dev)
+    ws = torch.empty(max(patchmatch_workspace_bytes(S, Hq, Wq), 1), dtype=torch.uint8, device=dev)
+    d = _native_width(d)
+    Q, K = _pad_channels(d, Q, K)
+    head = (_ptr(Q), _ptr(K), _dtype_code(Q), S, Hq, Wq, Hk, Wk, d, int(iters), int(seed) & 0xFFFFFFFFFFFFFFFF, None,
+            None, 1, int(flags) | (CAUSAL if causal else 0))
+    base, step, ws_ptr, ws_bytes = maps.data_ptr(), 4 * S * Hq * Wq, _ptr(ws), ws.numel()
+    for c in range(kappa):  # run c reads the maps of runs 0 .. c - 1
+        _call(lib().scram_patchmatch, "scram_patchmatch", dev,
+              (*head, base if c else None, c, int(sep), base + c * step, None, ws_ptr, ws_bytes, None))
     return maps
+
+
+def _paddable(*tensors) -> bool:
+    """Whether the calls take these tensors (contiguous [S, H, W, d] on one device, one type they know);
+    otherwise they say themselves what is wrong."""
+    torch = _torch()
+    q = tensors[0]
+    return all(t.is_cuda and t.dim() == 4 and t.is_contiguous() and t.dtype == q.dtype and t.device == q.device
+               for t in tensors) and q.dtype in (torch.float32, torch.bfloat16)
 
 
 def forward(Q, K, V, iters: int, seed: int, window: int, scale: float | None = None, *, kappa: int = 1,
             sep: int = 1, causal: bool = False):
     """The whole path: kappa argmax maps, then the sparse attention output over their windows."""
+    d, dv = Q.shape[-1], V.shape[-1]
+    w = _native_width(max(d, dv))
+    if d == dv < w and K.shape[-1] == d and _paddable(Q, K, V):  # once for every call below
+        scale = d ** -0.5 if scale is None else scale
+        Q, K, V = _pad_channels(w, Q, K, V)
     J = patchmatch_kappa(Q, K, kappa, iters, seed, sep=sep, causal=causal)
-    return sparse_attend(Q, K, V, J, window, scale, causal=causal), J
+    return _unpad_into(sparse_attend(Q, K, V, J, window, scale, causal=causal), dv), J

@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(LIB_DIR, "libscram.so")
 ORDER_LIB_PATH = os.path.join(LIB_DIR, "libscram_order.so")
 ORDER_DEFINES = ["-DSCRAM_LANE_TILE_SKEW=1", "-DSCRAM_BAND_TILES=3", "-DSCRAM_BAND_MAX=0", "-DSCRAM_XCD_REMAP=0"]
 SOURCES = [os.path.join(CSRC, f) for f in ("scram_pm.hip", "scram_attend.hip", "scram_backward.hip", "scram_snis.hip",
-                                             "scram_noalloc.hip", "scram_api.cpp")]
+                                             "scram_pad.hip", "scram_noalloc.hip", "scram_api.cpp")]
 ARCH = "gfx950"
 
 COMPILE_FLAGS = [

@@ -319,6 +319,28 @@ int scram_snis_attend(const void* Q, const void* K, const void* V, int dtype, co
     return e == hipSuccess ? SCRAM_OK : SCRAM_ERR_HIP;
 }
 
+int scram_pad_channels(int count, const void* const* src, void* const* dst, const int64_t* rows, const int* widths,
+                       int width, int elem_bytes, int unpad, hipStream_t stream)
+{
+    if (!src || !dst || !rows || !widths) return SCRAM_ERR_NULL;
+    if (count < 1 || count > 4) return SCRAM_ERR_SHAPE;
+    if (!supported_width(width) || (elem_bytes != 2 && elem_bytes != 4)) return SCRAM_ERR_UNSUPPORTED;
+    scram::PadTensor t[4];
+    for (int i = 0; i < count; ++i) {
+        if (!src[i] || !dst[i]) return SCRAM_ERR_NULL;
+        if (rows[i] < 1 || rows[i] >= (int64_t(1) << 40) / width || widths[i] < 1 || widths[i] > width)
+            return SCRAM_ERR_SHAPE;
+        const void* wide = unpad ? src[i] : dst[i];
+        const void* narrow = unpad ? dst[i] : src[i];
+        if (!aligned(wide, 16) || !aligned(narrow, elem_bytes)) return SCRAM_ERR_ALIGN;
+        const size_t row = size_t(rows[i]) * elem_bytes;
+        if (overlap(range(wide, row * width), range(narrow, row * widths[i]))) return SCRAM_ERR_ALIAS;
+        t[i] = scram::PadTensor{src[i], dst[i], rows[i], widths[i]};
+    }
+    const hipError_t e = scram::launch_pad(t, count, width, elem_bytes, unpad != 0, stream);
+    return e == hipSuccess ? SCRAM_OK : SCRAM_ERR_HIP;
+}
+
 const char* scram_status_string(int status)
 {
     switch (status) {

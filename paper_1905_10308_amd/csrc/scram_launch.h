@@ -80,6 +80,15 @@ hipError_t launch_snis(int dtype, const void* Q, const void* K, const void* V, c
                        const Grid& g, const SnisSpec& spec, bool causal, void* out, float* ess, float* var,
                        hipStream_t stream, hipEvent_t start, hipEvent_t stop);
 
+// Copies between rows of `width` elements and shorter rows (scram_pad_channels).
+struct PadTensor {
+    const void* src;
+    void* dst;
+    int64_t rows;
+    int width;  // of the short rows
+};
+hipError_t launch_pad(const PadTensor* t, int count, int width, int elem_bytes, bool unpad, hipStream_t stream);
+
 // Blocks (of 256 threads) of the largest dispatch an entry point makes for
 // this shape; 0 for an unsupported (dtype, d).  One dispatch holds at most
 // 2^32 - 1 work-items, so the front end rejects shapes above that.
