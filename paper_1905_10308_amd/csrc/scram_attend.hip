@@ -741,15 +741,17 @@ hipError_t run_attend_m(const AttParams& p, int window, uint64_t blocks, hipStre
 // The matrix-core kernel takes bf16 storage, windows of side 3, 5, 7 or 9 (up
 // to four maps, with or without the causal mask; with 32 or 64 channels and
 // windows up to 7 all kMaxKappa), a positive scale and slices of at most 4 GiB
-// of key rows; the lane-group kernels take every other call.  They also keep
-// one 3 x 3 window of 128 channels and all 3 x 3 windows of 16: their boxes
-// hold few rows that queries share (16 maps of 128 x 128: 24.9 us against 34.7
-// with 16 channels, half of them 38.7 against 43.8 with 128).  Measured over
-// the lane-group kernels (256 x 256 x 4 or 128 x 128 x 8 queries, us): 9 x 9
-// 202 -> 88 (64 channels), 63 -> 31 (32); 128 channels 5 x 5 70 -> 53, 7 x 7
-// 120 -> 65, causal 5 x 5 72 -> 49, three 9 x 9 windows 548 -> 127; 16
-// channels (four times the queries) 5 x 5 51 -> 45, 7 x 7 95 -> 61, 9 x 9
-// 150 -> 78.
+// of key rows; the lane-group kernels take every other call.  With 16 and 128
+// channels they also keep 3 x 3 windows and 5 x 5 ones, but for several 5 x 5
+// windows of 128 channels: those gain only
+// where neighbouring matches lie together (128 x 128 queries a slice, maps
+// displaced by up to 24 px that vary over 8 px: 5 x 5 70 -> 53 us with 128
+// channels, 51 -> 45 with 16) and lose where they do not (one 400 x 300 slice,
+// displaced by up to 60 px that vary over 4 px, 5 % elsewhere: 73 -> 83 us and
+// 25 -> 30).  The others gain on both: 128 channels 7 x 7 120 -> 65 and 121 ->
+// 112 us, two 5 x 5 windows 90 -> 49 (97 x 111 x 8) and 129 -> 97; 16 channels
+// 7 x 7 95 -> 61 and 46 -> 38; 9 x 9 of 64 channels 202 -> 88 (256 x 256 x 4)
+// and 109 -> 75, of 32 63 -> 31 and 87 -> 54.
 #ifndef SCRAM_ATTEND_TILE
 #define SCRAM_ATTEND_TILE 1
 #endif
@@ -764,7 +766,7 @@ hipError_t run_attend(const AttParams& p0, int window, hipStream_t st, hipEvent_
     if constexpr (kTileKernel<T, D>) {
         constexpr bool kMid = D == 32 || D == 64;
         const bool fits = kMid && window <= 7 ? p.kappa <= kMaxKappa : p.kappa <= 4;
-        const bool pays = kMid || window > 3 || (D == 128 && p.kappa > 1);
+        const bool pays = kMid || window > 5 || (D == 128 && window == 5 && p.kappa > 1);
         const uint64_t tiles = tiling_blocks(make_tiling(p.Hq, p.Wq, kBlock / 4), p.n / (static_cast<uint32_t>(p.Hq) * p.Wq));
         if (tiles <= kMaxBlocks && fits && pays && window >= 3 && window <= 9 && p.scale_log2e > 0.f &&
             static_cast<uint64_t>(p.nkeys) * (2 * D) <= 0xFFFFFFFFull) {

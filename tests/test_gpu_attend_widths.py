@@ -9,7 +9,7 @@ from gpu_util import TOL, row_rel_err, tile_maps, to_dev
 
 pytestmark = pytest.mark.gpu
 
-# 16 channels take the matrix cores from 5 x 5 on, 128 from 5 x 5 on or with several maps, 32 and 64 with 9 x 9 windows
+# 16 and 128 channels take the matrix cores from 7 x 7 on, 128 also with several 5 x 5 windows, 32 and 64 with 9 x 9 too
 SHAPES = [(16, 5), (16, 7), (16, 9), (32, 9), (64, 9), (128, 3), (128, 5), (128, 9)]
 # several tiles with ragged edges, the smallest grids, one row, one column, two grids
 GRIDS = [(2, 21, 37, 21, 37), (1, 3, 5, 3, 5), (1, 1, 50, 1, 50), (1, 50, 1, 50, 1), (1, 19, 11, 33, 30)]
