@@ -229,8 +229,8 @@ int scram_patchmatch_noalloc(const void* Q, const void* K, int dtype, int S, int
  *
  * Arguments:
  *   Q, K, V   inputs, layouts above; V has dv channels (dv == d); finite
- *             values (with bf16 storage and d of 32 or 64, the keys of
- *             neighbouring queries' windows are read in shared blocks in
+ *             values (with bf16 storage, d of 32 or 64 and a window of
+ *             side 3, 5 or 7, the keys of neighbouring queries' windows are read in shared blocks in
  *             which a key outside a query's window has weight 0, and
  *             0 * inf would reach that query)
  *   argmax    int32 [kappa, S, Hq, Wq] flat key indices (e.g. kappa runs of
@@ -260,9 +260,11 @@ int scram_sparse_attend(const void* Q, const void* K, const void* V, int dtype, 
  * weights are recomputed from Q, K, V (the forward output is not needed).
  * Key j lies in W_i exactly when a match of query i lies in the
  * (2b+1) x (2b+1) neighbourhood of j, so dK_j and dV_j gather over the
- * queries found through the inverse of the maps (kept in the workspace; for
- * fp32 storage and for windows of side 1 or above 15 the key side also copies
- * those queries' q, dO rows there in the inverse map's order).
+ * queries found through the inverse of the maps (kept in the workspace; where the
+ * key side does not run on the matrix cores -- windows of side 1 or above 15,
+ * and calls in fp32 with 1 x 1 key grids or with 128 channels in one map or
+ * below 7 x 7 -- it also copies those queries' q, dO rows there in the inverse
+ * map's order).
  * Every gradient row has a single writer; the order in which the queries of
  * one match key are summed is the order the inverse map was filled in,
  * which may differ between calls (dK, dV may differ in the last bits; dQ is
