@@ -262,8 +262,8 @@ int scram_sparse_attend(const void* Q, const void* K, const void* V, int dtype, 
  * (2b+1) x (2b+1) neighbourhood of j, so dK_j and dV_j gather over the
  * queries found through the inverse of the maps (kept in the workspace; where the
  * key side does not run on the matrix cores -- windows of side 1 or above 15,
- * and calls in fp32 with 1 x 1 key grids or with 128 channels in one map or
- * below 7 x 7 -- it also copies those queries' q, dO rows there in the inverse
+ * and calls in fp32 with 1 x 1 key grids, with 128 channels or with 64 and
+ * several maps -- it also copies those queries' q, dO rows there in the inverse
  * map's order).
  * Every gradient row has a single writer; the order in which the queries of
  * one match key are summed is the order the inverse map was filled in,

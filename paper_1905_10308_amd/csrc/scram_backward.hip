@@ -1164,7 +1164,6 @@ bwd_key_strip_f32_kernel(BwdParams p)
     constexpr int kLR = D / 4;     // lanes per staged row
     constexpr int kRpi = 64 / kLR; // rows per load instruction
     constexpr int kRep = kCE / kRpi;
-    constexpr bool kAhead = D <= 64;  // the next chunk's rows in registers during the products
     __shared__ __align__(16) float s_q[kCE * kRowF], s_g[kCE * kRowF];
     __shared__ int4 s_meta[kCE];  // match row, match column, lse2 bits, D bits
     __shared__ int32_t s_el[kQueryIndex ? kCE : 1][2];  // as in the bf16 kernel
@@ -1243,6 +1242,34 @@ bwd_key_strip_f32_kernel(BwdParams p)
 #pragma unroll
     for (int o = 0; o < kOt; ++o) dk[o] = dv[o] = zero;
 
+    // several maps: a strip's entries run to thousands, so the sums of every kRun chunks are added to the keys' rows
+    // in memory, which this wave alone writes (one long sum erred by up to 2 % more than the lane-group kernels,
+    // which share such keys among 8 groups; adding to memory costs 1-5 %)
+    constexpr int kRun = 8;
+    auto add_rows = [&](bool first) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            int ox, oy;
+            strip_key(4 * g4 + r, ox, oy);
+            if (ox >= p.Hk || oy >= p.Wk) continue;
+            const size_t row = (kslice + static_cast<size_t>(ox) * p.Wk + oy) * D + m * kOt;
+            float ok[kOt], ov[kOt];
+#pragma unroll
+            for (int o = 0; o < kOt; ++o) ok[o] = ov[o] = 0.f;
+            if (!first) {
+                load_floats<kOt>(ok, p.dK + row);
+                load_floats<kOt>(ov, p.dV + row);
+            }
+#pragma unroll
+            for (int o = 0; o < kOt; ++o) {
+                ok[o] += dk[o][r], ov[o] += dv[o][r];
+                dk[o][r] = dv[o][r] = 0.f;
+            }
+            store_floats<kOt>(p.dK + row, ok);
+            store_floats<kOt>(p.dV + row, ov);
+        }
+    };
+
     // lane l < 16 finds entry slot l of a chunk
     auto slot_code = [&](int c0) {
         const int v = c0 + m;
@@ -1283,10 +1310,9 @@ bwd_key_strip_f32_kernel(BwdParams p)
         }
     };
     code = slot_code(0);
-    if constexpr (kAhead) fetch();
+    fetch();
     int next = slot_code(kCE);
     for (int c0 = 0; c0 < E; c0 += kCE) {
-        if constexpr (!kAhead) fetch();
 #pragma unroll
         for (int j = 0; j < kRep; ++j) {
             *reinterpret_cast<f32x4_t*>(s_q + (er + kRpi * j) * kRowF + 4 * ep) = rq[j];
@@ -1325,7 +1351,7 @@ bwd_key_strip_f32_kernel(BwdParams p)
             s_meta[m] = meta;
         }
         code = next;
-        if (kAhead && c0 + kCE < E) fetch();
+        if (c0 + kCE < E) fetch();
         next = slot_code(c0 + 2 * kCE);
         wave_lds_sync();
 
@@ -1373,6 +1399,8 @@ bwd_key_strip_f32_kernel(BwdParams p)
                 dv[oh + o] += cv[o];
             }
         }
+        if constexpr (MULTI)
+            if (c0 % (kRun * kCE) == (kRun - 1) * kCE) add_rows(c0 < kRun * kCE);
         wave_lds_sync();  // this chunk's LDS reads come before the next chunk's writes
     }
 
@@ -1386,10 +1414,16 @@ bwd_key_strip_f32_kernel(BwdParams p)
         const size_t row = (kslice + static_cast<size_t>(ox) * p.Wk + oy) * D + m * kOt;
         float ok[kOt], ov[kOt];
 #pragma unroll
+        for (int o = 0; o < kOt; ++o) ok[o] = ov[o] = 0.f;
+        if (MULTI && E >= kRun * kCE - (kCE - 1)) {  // add_rows ran
+            load_floats<kOt>(ok, p.dK + row);
+            load_floats<kOt>(ov, p.dV + row);
+        }
+#pragma unroll
         for (int o = 0; o < kOt; ++o) {
-            finite = finite && fabsf(dk[o][r]) < INFINITY && fabsf(dv[o][r]) < INFINITY;
-            ok[o] = dk[o][r] * p.scale;
-            ov[o] = dv[o][r];
+            ok[o] += dk[o][r], ov[o] += dv[o][r];
+            finite = finite && fabsf(ok[o]) < INFINITY && fabsf(ov[o]) < INFINITY;
+            ok[o] *= p.scale;
         }
         store_floats<kOt>(p.dK + row, ok);
         store_floats<kOt>(p.dV + row, ov);
@@ -1904,16 +1938,18 @@ hipError_t run_backward(const BwdParams& p0, hipStream_t st, hipEvent_t* ev, Inv
     // key side on the matrix cores; a one-key window (b = 0, or fp32 and a one-key grid) stays on the
     // lane-group kernels, whose dp is the query kernel's own arithmetic, so that dS = p (dp - D) is exactly
     // 0 there
-    // (fp32 rows of 128 channels, whose fragments and sums overfill the registers, pay there only with several
-    // large windows: two maps, 7 x 7, 8 x 128 x 128: 2521 -> 1887 us; 3 x 3 569 -> 704)
-    constexpr bool kWideF32 = std::is_same<T, float>::value && D == 128;
+    // (fp32 rows of 128 channels, whose fragments and sums overfill the registers, stay there too: two maps, 7 x 7,
+    // 8 x 128 x 128 gained (2521 -> 1887 us), but 3 x 3 lost (569 -> 704) and so did small grids: 64 x 64 170 -> 291;
+    // and several maps of 64 channels: 4 x 80 x 86 7 x 7 319 -> 266, 3 x 3 114 -> 122, 64 x 64 141 -> 161)
+    const bool wide = std::is_same<T, float>::value && (D == 128 || (D == 64 && p.kappa > 1));
     const bool one_key = p.b == 0 || (std::is_same<T, float>::value && p.nkeys == 1);
-    if (!one_key && p.b <= kTileMaxB && !(kWideF32 && (p.kappa == 1 || p.b < 3))) {
+    if (!one_key && p.b <= kTileMaxB && !wide) {
         BwdParams pt = p;
         pt.tk = make_tiling(p.Hk, p.Wk, kTileKeys);
         const uint64_t tblocks = kStripWaves * tiling_blocks(pt.tk, p.keys_total / p.nkeys);
         if constexpr (std::is_same<T, float>::value) {
-            if (p.kappa > 1) return launch_wave(bwd_key_strip_f32_kernel<D, kStripMulti>, tblocks, st, k0, k1, pt);
+            if constexpr (D < 64)
+                if (p.kappa > 1) return launch_wave(bwd_key_strip_f32_kernel<D, kStripMulti>, tblocks, st, k0, k1, pt);
             if constexpr (D < 128)
                 return p.causal ? launch_wave(bwd_key_strip_f32_kernel<D, kStripCausal>, tblocks, st, k0, k1, pt)
                                 : launch_wave(bwd_key_strip_f32_kernel<D, kStripPlain>, tblocks, st, k0, k1, pt);
