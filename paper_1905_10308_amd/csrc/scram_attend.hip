@@ -702,6 +702,19 @@ attend_tile_kernel(AttParams p)
     if (!valid) return;
     const float lt = lacc[0];  // every row of the ones-block product holds query m's sum of weights
     const float inv = lt > 0.f ? __builtin_amdgcn_rcpf(lt) : 0.f;  // (1 ulp: far below the bf16 rounding)
+    if constexpr (D == 16 || D == 128 || W == 9) {
+        // the shapes whose inputs need not be finite.  A query's row is stored here or by attend_plain_row, never by
+        // both: their lanes hold different channels, and nothing would order the two stores
+        float t = lt;
+#pragma unroll
+        for (int o = 0; o < kOt; ++o) t += (fabsf(acc[o][0]) + fabsf(acc[o][1])) + (fabsf(acc[o][2]) + fabsf(acc[o][3]));
+        const uint64_t bad = __ballot(!(t < INFINITY));
+        const uint32_t of = static_cast<uint32_t>(bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xFFFFu;  // bit m: query m
+        if ((of >> m) & 1u) {
+            attend_plain_row<D, MK>(p, g, g4);
+            return;
+        }
+    }
     // lane holds channels 16 o + 4 g4 + i of query m; pairs rounded to bf16 (nearest even) together
     uint16_t* const orow = static_cast<uint16_t*>(p.out) + static_cast<size_t>(g) * D;
     auto bf2 = [](float a, float b) {
@@ -712,15 +725,6 @@ attend_tile_kernel(AttParams p)
         const uint32_t w0 = bf2(acc[o][0] * inv, acc[o][1] * inv);
         const uint32_t w1 = bf2(acc[o][2] * inv, acc[o][3] * inv);
         *reinterpret_cast<uint2*>(orow + 16 * o + 4 * g4) = make_uint2(w0, w1);
-    }
-    if constexpr (D == 16 || D == 128 || W == 9) {
-        // the shapes whose inputs need not be finite
-        float t = lt;
-#pragma unroll
-        for (int o = 0; o < kOt; ++o) t += (fabsf(acc[o][0]) + fabsf(acc[o][1])) + (fabsf(acc[o][2]) + fabsf(acc[o][3]));
-        const uint64_t bad = __ballot(!(t < INFINITY));
-        const uint32_t of = static_cast<uint32_t>(bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xFFFFu;  // bit m: query m
-        if ((of >> m) & 1u) attend_plain_row<D, MK>(p, g, g4);
     }
 }
 
