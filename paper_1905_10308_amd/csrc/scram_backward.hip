@@ -1242,33 +1242,13 @@ bwd_key_strip_f32_kernel(BwdParams p)
 #pragma unroll
     for (int o = 0; o < kOt; ++o) dk[o] = dv[o] = zero;
 
-    // several maps: a strip's entries run to thousands, so the sums of every kRun chunks are added to the keys' rows
-    // in memory, which this wave alone writes (one long sum erred by up to 2 % more than the lane-group kernels,
-    // which share such keys among 8 groups; adding to memory costs 1-5 %)
+    // several maps: a strip's entries run to thousands, so the sums of every kRun chunks go onto a second set (one long
+    // sum erred by up to 2 % more than the lane-group kernels, which share such keys among 8 groups)
     constexpr int kRun = 8;
-    auto add_rows = [&](bool first) {
+    constexpr int kTot = MULTI ? kOt : 1;
+    f32x4_t tk[kTot], tv[kTot];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            int ox, oy;
-            strip_key(4 * g4 + r, ox, oy);
-            if (ox >= p.Hk || oy >= p.Wk) continue;
-            const size_t row = (kslice + static_cast<size_t>(ox) * p.Wk + oy) * D + m * kOt;
-            float ok[kOt], ov[kOt];
-#pragma unroll
-            for (int o = 0; o < kOt; ++o) ok[o] = ov[o] = 0.f;
-            if (!first) {
-                load_floats<kOt>(ok, p.dK + row);
-                load_floats<kOt>(ov, p.dV + row);
-            }
-#pragma unroll
-            for (int o = 0; o < kOt; ++o) {
-                ok[o] += dk[o][r], ov[o] += dv[o][r];
-                dk[o][r] = dv[o][r] = 0.f;
-            }
-            store_floats<kOt>(p.dK + row, ok);
-            store_floats<kOt>(p.dV + row, ov);
-        }
-    };
+    for (int o = 0; o < kTot; ++o) tk[o] = tv[o] = zero;
 
     // lane l < 16 finds entry slot l of a chunk
     auto slot_code = [&](int c0) {
@@ -1399,41 +1379,50 @@ bwd_key_strip_f32_kernel(BwdParams p)
                 dv[oh + o] += cv[o];
             }
         }
-        if constexpr (MULTI)
-            if (c0 % (kRun * kCE) == (kRun - 1) * kCE) add_rows(c0 < kRun * kCE);
+        if constexpr (MULTI) {
+            if (c0 % (kRun * kCE) == (kRun - 1) * kCE) {
+#pragma unroll
+                for (int o = 0; o < kOt; ++o) {
+                    tk[o] += dk[o], tv[o] += dv[o];
+                    dk[o] = dv[o] = zero;
+                }
+            }
+        }
         wave_lds_sync();  // this chunk's LDS reads come before the next chunk's writes
     }
+    if constexpr (MULTI) {
+#pragma unroll
+        for (int o = 0; o < kOt; ++o) dk[o] += tk[o], dv[o] += tv[o];
+    }
 
-    // lane holds keys 4 g4 + r of the strip, channels m D / 16 + o
-    bool finite = true;
+    // lane holds keys 4 g4 + r of the strip, channels m D / 16 + o.  A key's rows are stored here or by key_grads_plain,
+    // never by both: their lanes hold different channels, and nothing would order the two stores
+    uint32_t bad = 0u;  // bit i: key i's sums are not finite
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        bool finite = true;
+#pragma unroll
+        for (int o = 0; o < kOt; ++o) finite = finite && fabsf(dk[o][r]) < INFINITY && fabsf(dv[o][r]) < INFINITY;
+        const uint64_t not_finite = __ballot(!finite);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) bad |= ((not_finite >> (16 * g)) & 0xFFFFu) != 0u ? 1u << (4 * g + r) : 0u;
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         int ox, oy;
         strip_key(4 * g4 + r, ox, oy);
-        if (ox >= p.Hk || oy >= p.Wk) continue;
+        if (ox >= p.Hk || oy >= p.Wk || ((bad >> (4 * g4 + r)) & 1u)) continue;
         const size_t row = (kslice + static_cast<size_t>(ox) * p.Wk + oy) * D + m * kOt;
         float ok[kOt], ov[kOt];
 #pragma unroll
-        for (int o = 0; o < kOt; ++o) ok[o] = ov[o] = 0.f;
-        if (MULTI && E >= kRun * kCE - (kCE - 1)) {  // add_rows ran
-            load_floats<kOt>(ok, p.dK + row);
-            load_floats<kOt>(ov, p.dV + row);
-        }
-#pragma unroll
-        for (int o = 0; o < kOt; ++o) {
-            ok[o] += dk[o][r], ov[o] += dv[o][r];
-            finite = finite && fabsf(ok[o]) < INFINITY && fabsf(ov[o]) < INFINITY;
-            ok[o] *= p.scale;
-        }
+        for (int o = 0; o < kOt; ++o) ok[o] = dk[o][r] * p.scale, ov[o] = dv[o][r];
         store_floats<kOt>(p.dK + row, ok);
         store_floats<kOt>(p.dV + row, ov);
     }
-    if (__any(!finite)) {
-        for (int i = 0; i < 16; ++i) {
-            int ox, oy;
-            strip_key(i, ox, oy);
-            if (ox < p.Hk && oy < p.Wk) key_grads_plain<D>(p, s, ox, oy, lane);
-        }
+    for (; bad != 0u; bad &= bad - 1u) {
+        int ox, oy;
+        strip_key(__builtin_ctz(bad), ox, oy);
+        if (ox < p.Hk && oy < p.Wk) key_grads_plain<D>(p, s, ox, oy, lane);
     }
 }
 

@@ -55,3 +55,49 @@ def test_non_finite_gradients_stay_with_their_keys(scram, d):
         # the same sums in either order of the entries
         assert torch.allclose(g[~near], c[~near], rtol=1e-5, atol=2e-5 * float(c.abs().max()))
         assert (~torch.isfinite(g[near])).any(dim=-1).all()
+
+
+def key_sets(J, H, W, window, causal):
+    """[queries, keys] of one slice: whether the union of the query's windows holds the key."""
+    b, n = window // 2, H * W
+    k = np.arange(n)
+    held = np.zeros((n, n), bool)
+    for m in J.reshape(len(J), n):
+        held |= (np.abs(m[:, None] // W - k[None] // W) <= b) & (np.abs(m[:, None] % W - k[None] % W) <= b)
+    return held & (k[None] <= k[:, None]) if causal else held
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,kappa,window", [(16, 1, 5), (16, 3, 3), (32, 2, 5), (32, 3, 7), (64, 1, 7)])
+def test_non_finite_gradients_of_unions(scram, d, kappa, window, causal):
+    """The same with several maps, the causal mask and keys that gather hundreds of entries (more than the 128
+    that are summed in one run): the keys of the affected queries' sets, and no others."""
+    H, W = 24, 24
+    rng = np.random.default_rng(d + kappa)
+    Q, K, V, dO = (rng.standard_normal((1, H, W, d)).astype(np.float32) for _ in range(4))
+    own = np.arange(H * W).reshape(1, H, W)
+    # the queries' own keys, then three quarters of the queries at one key (an early one, so that the mask keeps it)
+    many = np.where(rng.random((1, H, W)) < 0.75, 2 * W + 3, rng.integers(0, H * W, (1, H, W)))
+    J = np.stack([many, own, np.roll(own, 5, 2)][:kappa]).astype(np.int32)
+    ref = oracle.sparse_attend_backward(Q, K, V, J, window, d ** -0.5, dO, flags=oracle.CAUSAL if causal else 0)
+    bad = {17 * W + 20: (3, np.inf), 9 * W + 6: (d - 1, np.nan)}
+    for q, (ch, x) in bad.items():
+        dO[0, q // W, q % W, ch] = x
+    got = scram.sparse_attend_backward(*(to_dev(x, "f32") for x in (Q, K, V)), torch.from_numpy(J).cuda(),
+                                       to_dev(dO, "f32"), window, causal=causal)
+    held = key_sets(J, H, W, window, causal)
+    assert max(held.sum(0)) > 3 * 128
+    near = held[list(bad)].any(0)
+    assert near.any() and not near.all()
+    for name, g, r in zip(("dK", "dV"), got[1:], ref[1:]):
+        g, r = g.double().cpu().numpy().reshape(H * W, d), r.reshape(H * W, d)
+        assert np.isfinite(g[~near]).all(), name
+        assert np.abs(g[~near] - r[~near]).max() <= 2e-5 * np.abs(r).max(), name
+        assert (~np.isfinite(g[near])).any(1).all(), name
+    # dV of a key in a set is not finite in that channel, and only there
+    dv = got[2].cpu().numpy().reshape(H * W, d)
+    for q, (ch, _) in bad.items():
+        assert not np.isfinite(dv[held[q], ch]).any()
+    rest = np.ones(d, bool)
+    rest[[ch for ch, _ in bad.values()]] = False
+    assert np.isfinite(dv[:, rest]).all()
