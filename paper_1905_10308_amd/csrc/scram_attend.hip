@@ -260,13 +260,17 @@ __global__ __launch_bounds__(kBlock) void attend_kernel(AttParams p)
 // second holding back the keys of the first's windows): each
 // window is kept in the box of its own centre's cluster, less the keys of
 // the query's earlier windows (and of those after the query).
-// One query's row key by key, for lanes (m, 0 .. 3) of a wave: what the lane-group kernels compute.  The matrix-core
-// kernel takes it for a query whose result is not finite, since a non-finite value row of the box reaches every query of the
-// cluster through 0 * inf, also one whose window does not hold it.
-template <int D, int MK>
+//
+// One query's row key by key, for lanes (m, 0 .. 3) of a wave.  The matrix-core kernel takes it for a query whose
+// result is not finite, since a non-finite value row of the box reaches every query of the cluster through 0 * inf,
+// also one whose window does not hold it.  Scores that are NaN count as in the lane-group kernels, which raise the
+// reference a batch at a time (a window row; 4 slots of windows above 7 x 7): a batch without any score that is a
+// number is left out while there is no reference, in any other a NaN score makes the row NaN.
+template <int D, int W, int MK>
 __device__ void attend_plain_row(const AttParams& p, uint32_t g, int g4)
 {
     using TR = TileRow<D>;
+    constexpr int B = W / 2;
     uint32_t s, rem;
     divmod(g, p.div_plane, s, rem);
     const unsigned char* const Kb = static_cast<const unsigned char*>(p.K) + static_cast<size_t>(s) * p.nkeys * (2 * D);
@@ -286,10 +290,14 @@ __device__ void attend_plain_row(const AttParams& p, uint32_t g, int g4)
     for (int e = 0; e < p.kappa; ++e) {
         uint32_t u, v;
         ws.centre(e, u, v);
-        const int r0 = max(static_cast<int>(u) - p.b, 0), r1 = min(static_cast<int>(u) + p.b, p.Hk - 1);
-        const int c0 = max(static_cast<int>(v) - p.b, 0), c1 = min(static_cast<int>(v) + p.b, p.Wk - 1);
-        for (int r = r0; r <= r1; ++r)
-            for (int c = c0; c <= c1; ++c) {
+        const int r0 = max(static_cast<int>(u) - B, 0), r1 = min(static_cast<int>(u) + B, p.Hk - 1);
+        const int c0 = max(static_cast<int>(v) - B, 0), c1 = min(static_cast<int>(v) + B, p.Wk - 1);
+        const int nc = c1 - c0 + 1, nwin = (r1 - r0 + 1) * nc;
+        const int step = W <= 7 ? nc : 4;  // slots per batch
+        // fn(byte offset, score) for the batch's keys of the set
+        auto batch = [&](int k0, auto&& fn) {
+            for (int k = k0; k < min(k0 + step, nwin); ++k) {
+                const int r = r0 + k / nc, c = c0 + k % nc;
                 if (ws.skip(e, r, c)) continue;
                 const uint32_t off = static_cast<uint32_t>(r * p.Wk + c) * (2u * D);
                 float sc = 0.f;
@@ -297,18 +305,23 @@ __device__ void attend_plain_row(const AttParams& p, uint32_t g, int g4)
                 for (int ds = 0; ds < TR::kDs; ++ds) sc = TR::dot(q[ds], TR::frag(Kb + off, ds, g4), sc);
                 sc += __shfl_xor(sc, 16);
                 sc += __shfl_xor(sc, 32);
-                sc *= p.scale_log2e;
-                const float mb = fmaxf(m, sc);
-                if (mb == -INFINITY) continue;
-                if (mb > m + kRescaleSlack) {
-                    const float alpha = __builtin_amdgcn_exp2f(m - mb);
-                    l *= alpha;
+                fn(off, sc * p.scale_log2e);
+            }
+        };
+        for (int k0 = 0; k0 < nwin; k0 += step) {
+            float mb = m;
+            batch(k0, [&](uint32_t, float sc) { mb = fmaxf(mb, sc); });
+            if (mb == -INFINITY) continue;
+            if (mb > m + kRescaleSlack) {
+                const float alpha = __builtin_amdgcn_exp2f(m - mb);
+                l *= alpha;
 #pragma unroll
-                    for (int ds = 0; ds < TR::kDs; ++ds)
+                for (int ds = 0; ds < TR::kDs; ++ds)
 #pragma unroll
-                        for (int i = 0; i < kE; ++i) acc[ds][i] *= alpha;
-                    m = mb;
-                }
+                    for (int i = 0; i < kE; ++i) acc[ds][i] *= alpha;
+                m = mb;
+            }
+            batch(k0, [&](uint32_t off, float sc) {
                 const float pj = __builtin_amdgcn_exp2f(sc - m);
                 l += pj;
 #pragma unroll
@@ -317,7 +330,8 @@ __device__ void attend_plain_row(const AttParams& p, uint32_t g, int g4)
 #pragma unroll
                     for (int i = 0; i < kE; ++i) acc[ds][i] = fmaf(pj, static_cast<float>(vr[i]), acc[ds][i]);
                 }
-            }
+            });
+        }
     }
     const float inv = l > 0.f ? 1.f / l : 0.f;
     uint16_t* const orow = static_cast<uint16_t*>(p.out) + static_cast<size_t>(g) * D;
@@ -711,7 +725,7 @@ attend_tile_kernel(AttParams p)
         const uint64_t bad = __ballot(!(t < INFINITY));
         const uint32_t of = static_cast<uint32_t>(bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xFFFFu;  // bit m: query m
         if ((of >> m) & 1u) {
-            attend_plain_row<D, MK>(p, g, g4);
+            attend_plain_row<D, W, MK>(p, g, g4);
             return;
         }
     }

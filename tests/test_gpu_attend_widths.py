@@ -104,3 +104,56 @@ def test_non_finite_values_stay_in_their_channels(scram, d, window, kappa, causa
             off[key_sets(J, H, W, window, False)[:, k] & ~np.isfinite(got[:, ch]), ch] = True
     np.testing.assert_array_equal(~np.isfinite(got), off)
     np.testing.assert_allclose(got[~off], clean[~off], rtol=2 ** -7, atol=1e-3)  # (bf16 rounding of either path)
+
+
+def attend_by_batches(q, K, V, J, i, H, W, window, scale, causal):
+    """Query i's row in fp64 (K, V: [keys, d]; J: [kappa, queries]) as the lane-group kernels define it for scores
+    that are not finite: the reference is raised a batch of keys at a time (a window row; 4 slots of windows above
+    7 x 7), and a batch without a score that is a number is left out while there is no reference."""
+    b, kept, seen, poisoned, ref = window // 2, [], set(), False, -np.inf
+    for m in J[:, i]:
+        u, v = divmod(int(m), W)
+        rows = [[r * W + c for c in range(max(v - b, 0), min(v + b, W - 1) + 1)]
+                for r in range(max(u - b, 0), min(u + b, H - 1) + 1)]
+        slots = sum(rows, [])
+        batches = rows if window <= 7 else [slots[k:k + 4] for k in range(0, len(slots), 4)]
+        for batch in batches:
+            keys = [k for k in batch if k not in seen and not (causal and k > i)]
+            if not keys:
+                continue
+            sc = K[keys] @ q * scale
+            ref = max([ref, *sc[~np.isnan(sc)]])
+            if ref == -np.inf:
+                continue
+            poisoned |= bool(np.isnan(sc).any() or ref == np.inf)
+            kept += [(k, x) for k, x in zip(keys, sc) if x > -np.inf]
+        seen |= set(slots)
+    if poisoned:
+        return np.full(V.shape[1], np.nan)
+    if not kept:
+        return np.zeros(V.shape[1])
+    w = np.exp(np.array([x for _, x in kept]) - max(x for _, x in kept))
+    return (w / w.sum()) @ V[[k for k, _ in kept]]
+
+
+@pytest.mark.parametrize("d,window", SHAPES)
+@pytest.mark.parametrize("kappa", [1, 2, 3])
+@pytest.mark.parametrize("causal", [False, True])
+def test_scores_that_are_not_finite(scram, d, window, kappa, causal):
+    """A key row with a NaN (every score of the key is NaN) or an infinity (scores of either sign) counts wherever
+    it lies in a window -- its first key, its last, one between -- and not outside; a query of NaNs has no score."""
+    H, W, Q, K, V, J = unit_case(d, kappa, 3 * d + window + kappa)
+    K[0, 0, 0, 1] = K[0, 9, 13, d - 1] = np.nan
+    K[0, 15, 6, d // 2] = np.inf
+    Q[0, 20, 20] = np.nan
+    got = scram.sparse_attend(*(to_dev(x, "bf16") for x in (Q, K, V)), torch.from_numpy(J).cuda(), window, causal=causal)
+    got = got.double().cpu().numpy().reshape(H * W, d)
+    Qf, Kf, Vf = (x.astype(np.float64).reshape(H * W, d) for x in (Q, K, V))
+    with np.errstate(invalid="ignore"):
+        ref = np.stack([attend_by_batches(Qf[i], Kf, Vf, J.reshape(kappa, -1), i, H, W, window, d ** -0.5, causal)
+                        for i in range(H * W)])
+    nan = np.isnan(ref).any(1)
+    assert nan.any() and not nan.all()
+    np.testing.assert_array_equal(np.isnan(got).all(1), nan)
+    assert np.isfinite(got[~nan]).all()
+    assert row_rel_err(got[~nan], ref[~nan]).max() <= TOL["bf16"]
