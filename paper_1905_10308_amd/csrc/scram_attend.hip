@@ -242,7 +242,8 @@ __global__ __launch_bounds__(kBlock) void attend_kernel(AttParams p)
 //                            one channel, the operand layout that matches P^T,
 //                            and P enters as two bf16 parts (top 8 significant
 //                            bits, then the top 8 of the rest), so its relative
-//                            error is below 2^-16
+//                            error is below 2^-16, or as three that add up to it
+//                            (full_weights)
 // The softmax reference of a query starts at the score of its match (a key of
 // its window) and is raised (and its sums rescaled) only when a score passes
 // it by more than kRescaleSlack, as in the other kernels;
@@ -352,6 +353,11 @@ constexpr int tile_waves(int D, bool causal, int MK)
     return MK > 4 || (MK == 4 && causal) ? 3 : causal || MK > 1 ? 4 : 5;
 }
 
+// The shapes whose weights keep all 24 bits, as three bf16 parts and with a
+// sum in fp32, and whose inputs need not be finite, as on the lane-group
+// kernels that also serve such calls; the others hold two parts (16 bits).
+constexpr bool full_weights(int D, int W) { return D == 16 || D == 128 || W == 9; }
+
 template <int D, int W, bool CAUSAL, int MK>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(tile_waves(D, CAUSAL, MK)))) void
 attend_tile_kernel(AttParams p)
@@ -363,6 +369,7 @@ attend_tile_kernel(AttParams p)
     constexpr int kOt = D / 16;        // 16-channel tiles of O^T
     constexpr int kRowB = 2 * D + 16;  // LDS row stride: the 16-byte pad spreads a column read over the banks
     constexpr int kWaves = kBlock / 64;
+    constexpr bool kFull = full_weights(D, W);
     __shared__ __align__(16) unsigned char s_k[kWaves][16 * kRowB], s_v[kWaves][16 * kRowB];
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -470,7 +477,9 @@ attend_tile_kernel(AttParams p)
 #pragma unroll
     for (int o = 0; o < kOt; ++o) acc[o] = zero;
     // the softmax denominators: an all-ones row block times P^T sums P over the keys, for every query
+    // (kFull: the sum of this lane's keys of query m, in fp32)
     f32x4_t lacc = zero;
+    float lsum = 0.f;
     const bf16x4_t ones = bf16x4_t{static_cast<__bf16>(1.f), static_cast<__bf16>(1.f), static_cast<__bf16>(1.f),
                                    static_cast<__bf16>(1.f)};
     const float sl2e = p.scale_log2e;  // > 0 (the caller routes other scales to the lane-group kernels)
@@ -580,7 +589,10 @@ attend_tile_kernel(AttParams p)
             mx = fmaxf(mx, __shfl_xor(mx, 32));
             if (mx > mref + kRescaleSlack) {
                 const float alpha = __builtin_amdgcn_exp2f(mref - mx);
-                lacc *= alpha;
+                if constexpr (kFull)
+                    lsum *= alpha;
+                else
+                    lacc *= alpha;
 #pragma unroll
                 for (int o = 0; o < kOt; ++o) acc[o] *= alpha;
                 mref = mx;
@@ -589,26 +601,38 @@ attend_tile_kernel(AttParams p)
                 if constexpr (MK > 1) thr_q = thr;  // the query's later windows start from here
             }
         }
-        uint32_t ph[4], pl[4];
+        uint32_t ph[4], pm[4], pl[4];
+        float pk[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             // exponent of the window's slots; -inf (a weight of 0) elsewhere
             const uint32_t x = __float_as_uint(fmaf(sc[i], sl2e, nref));
-            const float pk = __builtin_amdgcn_exp2f(__uint_as_float((x & keep[i]) | (0xFF800000u & ~keep[i])));
-            ph[i] = __float_as_uint(pk) & 0xFFFF0000u;
-            pl[i] = __float_as_uint(pk - __uint_as_float(ph[i]));
+            pk[i] = __builtin_amdgcn_exp2f(__uint_as_float((x & keep[i]) | (0xFF800000u & ~keep[i])));
+            ph[i] = __float_as_uint(pk[i]) & 0xFFFF0000u;
+            pl[i] = __float_as_uint(pk[i] - __uint_as_float(ph[i]));
+            if constexpr (kFull) {
+                pm[i] = pl[i] & 0xFFFF0000u;
+                pl[i] = __float_as_uint(__uint_as_float(pl[i]) - __uint_as_float(pm[i]));
+            }
         }
-        const bf16x4_t pth =
-            __builtin_bit_cast(bf16x4_t, make_uint2(hi16_pair(ph[0], ph[1]), hi16_pair(ph[2], ph[3])));
-        const bf16x4_t ptl =
-            __builtin_bit_cast(bf16x4_t, make_uint2(hi16_pair(pl[0], pl[1]), hi16_pair(pl[2], pl[3])));
-        lacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, pth, lacc, 0, 0, 0);
-        lacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, ptl, lacc, 0, 0, 0);
+        auto part = [](const uint32_t (&x)[4]) {
+            return __builtin_bit_cast(bf16x4_t, make_uint2(hi16_pair(x[0], x[1]), hi16_pair(x[2], x[3])));
+        };
+        const bf16x4_t pth = part(ph), ptl = part(pl);
+        bf16x4_t ptm = ptl;
+        if constexpr (kFull) {
+            ptm = part(pm);
+            lsum += (pk[0] + pk[1]) + (pk[2] + pk[3]);
+        } else {
+            lacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, pth, lacc, 0, 0, 0);
+            lacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, ptl, lacc, 0, 0, 0);
+        }
 #pragma unroll
         for (int o = 0; o < kOt; ++o) {
             const bf16x4_t vt = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
                 (__attribute__((address_space(3))) bf16x4_t*)(tvt + 32 * o));
             acc[o] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, pth, acc[o], 0, 0, 0);
+            if constexpr (kFull) acc[o] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, ptm, acc[o], 0, 0, 0);
             acc[o] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, ptl, acc[o], 0, 0, 0);
         }
     };
@@ -713,11 +737,16 @@ attend_tile_kernel(AttParams p)
             wave_lds_sync();  // the last block's LDS reads come before the next pass's writes
         }
     }
+    float lt = lacc[0];  // every row of the ones-block product holds query m's sum of weights
+    if constexpr (kFull) {
+        lt = lsum + __shfl_xor(lsum, 16);
+        lt += __shfl_xor(lt, 32);
+    }
     if (!valid) return;
-    const float lt = lacc[0];  // every row of the ones-block product holds query m's sum of weights
-    const float inv = lt > 0.f ? __builtin_amdgcn_rcpf(lt) : 0.f;  // (1 ulp: far below the bf16 rounding)
-    if constexpr (D == 16 || D == 128 || W == 9) {
-        // the shapes whose inputs need not be finite.  A query's row is stored here or by attend_plain_row, never by
+    // (two parts: a reciprocal within 1 ulp is far below their error)
+    const float inv = lt > 0.f ? (kFull ? 1.f / lt : __builtin_amdgcn_rcpf(lt)) : 0.f;
+    if constexpr (kFull) {
+        // A query's row is stored here or by attend_plain_row, never by
         // both: their lanes hold different channels, and nothing would order the two stores
         float t = lt;
 #pragma unroll

@@ -157,3 +157,49 @@ def test_scores_that_are_not_finite(scram, d, window, kappa, causal):
     np.testing.assert_array_equal(np.isnan(got).all(1), nan)
     assert np.isfinite(got[~nan]).all()
     assert row_rel_err(got[~nan], ref[~nan]).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("d,window", SHAPES)
+@pytest.mark.parametrize("kappa", [1, 2])
+def test_weights_keep_24_bits(scram, d, window, kappa):
+    """Windows of three keys that count (scores 0, 0, x; the others' weights underflow to 0) with values -hi, -mid and
+    1, where hi and mid are the first and the second 8 significant bits of w = 2^x: the row is (w - hi - mid) / (2 + w),
+    the last 8 bits of w, and zero or worse where a weight holds 16 bits.  Bound: 2^x, its exponent's rounding and
+    the three sums err by at most 4 units of w's last place, the output by 2^-8 of itself."""
+    step, n = window + 1, 4
+    H = W = step * n
+    scale = 2.0 ** -3
+    per = scale * 1.4426950408889634  # log2 of a weight per unit of the score q . k
+    x = -np.arange(1, n * n + 1) / 16 - 0.03125
+    score = synth._round_bf16((x / per).astype(np.float32)).astype(np.float64)
+    w = np.exp2(score * per)  # (0.5, 1) and below: 24 bits
+    ulp = np.exp2(np.floor(np.log2(w)) - 23)
+
+    def cut(a):  # the top 8 significant bits
+        return (a.astype(np.float32).view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32).astype(np.float64)
+
+    hi = cut(w)
+    mid = cut(w - hi)
+    want = (w - hi - mid) / (2 + w)
+    K, V = (np.zeros((1, H, W, d), np.float32) for _ in range(2))
+    K[..., 0] = -4096.0  # a weight of 2^-738: 0
+    centre = np.zeros(n * n, np.int64)
+    for t in range(n * n):
+        u, v = (t // n) * step + step // 2, (t % n) * step + step // 2
+        centre[t] = u * W + v
+        for c, (s, val) in enumerate([(0.0, -hi[t]), (0.0, -mid[t]), (score[t], 1.0)]):
+            K[0, u, v + c - 1, 0] = s
+            V[0, u, v + c - 1] = val
+    Q = np.zeros((1, H, W, d), np.float32)
+    Q[..., 0] = 1.0
+    t = np.arange(H * W) % (n * n)
+    J = np.broadcast_to(centre[t].reshape(1, 1, H, W), (kappa, 1, H, W)).astype(np.int32)
+    dev = [to_dev(a, "bf16") for a in (Q, K, V)]
+    for a, b in zip(dev, (Q, K, V)):
+        assert np.array_equal(a.float().cpu().numpy(), b)  # (exact in bf16)
+    got = scram.sparse_attend(*dev, torch.from_numpy(np.ascontiguousarray(J)).cuda(), window, scale)
+    got = got.double().cpu().numpy().reshape(H * W, d)
+    sharp = (want > 32 * ulp)[t]
+    assert sharp.sum() >= H * W // 4
+    err = np.abs(got - want[t][:, None])
+    assert (err <= (4 * ulp / (2 + w) + 2.0 ** -8 * want)[t][:, None])[sharp].all(), err[sharp].max()
