@@ -21,6 +21,7 @@ struct AttParams {
     int causal;           // drop keys after the query (raster order)
     int Hq, Wq;
     Tiling tq;            // blocks -> tiles of the query grid (set per storage type and width)
+    int tile_blocks;      // most blocks of 16 keys a wave walks on the matrix cores
 };
 
 // ---------------------------------------------------------------------------
@@ -262,94 +263,146 @@ __global__ __launch_bounds__(kBlock) void attend_kernel(AttParams p)
 // window is kept in the box of its own centre's cluster, less the keys of
 // the query's earlier windows (and of those after the query).
 //
-// One query's row key by key, for lanes (m, 0 .. 3) of a wave.  The matrix-core kernel takes it for a query whose
-// result is not finite, since a non-finite value row of the box reaches every query of the cluster through 0 * inf,
-// also one whose window does not hold it.  Scores that are NaN count as in the lane-group kernels, which raise the
-// reference a batch at a time (a window row; 4 slots of windows above 7 x 7): a batch without any score that is a
-// number is left out while there is no reference, in any other a NaN score makes the row NaN.
-template <int D, int W, int MK>
-__device__ void attend_plain_row(const AttParams& p, uint32_t g, int g4)
+// Queries one by one, a lane group each, as the lane-group kernels compute them.  The matrix-core kernel takes this for
+// a wave whose matches lie too far apart for its queries to share rows, and for a query whose result is not finite, since
+// a non-finite value row of the box reaches every query of the cluster through 0 * inf, also one whose window does not
+// hold it.  The reference is raised a batch at a time (a window row; 4 slots
+// of windows above 7 x 7), which also says what a NaN score does: a batch without any score that is a number is left
+// out while there is no reference, in any other a NaN score makes the row NaN.  A value row that the causal mask
+// drops does not reach the query.
+template <int D>
+constexpr int kQueryLanes = D == 16 ? 2 : D == 128 ? 8 : 4;  // 16 bytes of a row per lane, 32 of 64 and 128 channels
+
+template <int D, int W, bool CAUSAL, int MK>
+__device__ __forceinline__ void attend_query(const AttParams& p, uint32_t g, int lane)
 {
-    using TR = TileRow<D>;
+    constexpr int G = kQueryLanes<D>;
+    constexpr bool MULTI = CAUSAL || MK > 1;
+    using T = uint16_t;
+    using RW = Row<T, D, G>;
+    constexpr int CH = RW::kCh;
+    constexpr int E = CH * RW::kEpc;
     constexpr int B = W / 2;
+    constexpr bool kRows = W <= 7;
+    constexpr int kNb = kRows ? W : 4;
     uint32_t s, rem;
     divmod(g, p.div_plane, s, rem);
-    const unsigned char* const Kb = static_cast<const unsigned char*>(p.K) + static_cast<size_t>(s) * p.nkeys * (2 * D);
-    const unsigned char* const Vb = static_cast<const unsigned char*>(p.V) + static_cast<size_t>(s) * p.nkeys * (2 * D);
-    constexpr int kE = TR::kPb / 2;  // channels per piece
-    typename TR::Frag q[TR::kDs];
-    float acc[TR::kDs][kE];
-    const unsigned char* const qrow = static_cast<const unsigned char*>(p.Q) + static_cast<size_t>(g) * (2 * D);
-#pragma unroll
-    for (int ds = 0; ds < TR::kDs; ++ds) {
-        q[ds] = TR::frag(qrow, ds, g4);
-#pragma unroll
-        for (int i = 0; i < kE; ++i) acc[ds][i] = 0.f;
-    }
-    const WindowSet<MK> ws = make_window_set<MK>(p, g, rem);
+    const size_t slice = static_cast<size_t>(s) * p.nkeys * D;
+    const T* const Ks = static_cast<const T*>(p.K) + slice;
+    const T* const Vs = static_cast<const T*>(p.V) + slice;
+    uint4 q[CH];
+    load_row<T, D, G>(static_cast<const T*>(p.Q), g, lane, q);
+    WindowSet<MK> ws;
+    if constexpr (MULTI) ws = make_window_set<MK>(p, g, rem);
+
     float m = -INFINITY, l = 0.f;
-    for (int e = 0; e < p.kappa; ++e) {
-        uint32_t u, v;
-        ws.centre(e, u, v);
-        const int r0 = max(static_cast<int>(u) - B, 0), r1 = min(static_cast<int>(u) + B, p.Hk - 1);
-        const int c0 = max(static_cast<int>(v) - B, 0), c1 = min(static_cast<int>(v) + B, p.Wk - 1);
-        const int nc = c1 - c0 + 1, nwin = (r1 - r0 + 1) * nc;
-        const int step = W <= 7 ? nc : 4;  // slots per batch
-        // fn(byte offset, score) for the batch's keys of the set
-        auto batch = [&](int k0, auto&& fn) {
-            for (int k = k0; k < min(k0 + step, nwin); ++k) {
-                const int r = r0 + k / nc, c = c0 + k % nc;
-                if (ws.skip(e, r, c)) continue;
-                const uint32_t off = static_cast<uint32_t>(r * p.Wk + c) * (2u * D);
-                float sc = 0.f;
+    float acc[E];
 #pragma unroll
-                for (int ds = 0; ds < TR::kDs; ++ds) sc = TR::dot(q[ds], TR::frag(Kb + off, ds, g4), sc);
-                sc += __shfl_xor(sc, 16);
-                sc += __shfl_xor(sc, 32);
-                fn(off, sc * p.scale_log2e);
-            }
+    for (int i = 0; i < E; ++i) acc[i] = 0.f;
+    // the keys key[] of the set's window e, those with use[]
+    auto batch = [&](const uint32_t (&key)[kNb], const bool (&use)[kNb]) {
+        // (rows of 7 keys, and of 5 with 128 channels: the values after the scores, for the matrix cores' registers)
+        constexpr bool kApart = kNb * CH >= 7 && kRows;
+        uint4 kr[kNb][CH], vr[kNb][CH];
+        auto values = [&]() {
+#pragma unroll
+            for (int c = 0; c < kNb; ++c) load_row<T, D, G>(Vs, key[c], lane, vr[c]);
         };
-        for (int k0 = 0; k0 < nwin; k0 += step) {
-            float mb = m;
-            batch(k0, [&](uint32_t, float sc) { mb = fmaxf(mb, sc); });
-            if (mb == -INFINITY) continue;
-            if (mb > m + kRescaleSlack) {
-                const float alpha = __builtin_amdgcn_exp2f(m - mb);
-                l *= alpha;
 #pragma unroll
-                for (int ds = 0; ds < TR::kDs; ++ds)
+        for (int c = 0; c < kNb; ++c) load_row<T, D, G>(Ks, key[c], lane, kr[c]);
+        if constexpr (!kApart) values();
+        float sc[kNb];
+        float mb = m;
 #pragma unroll
-                    for (int i = 0; i < kE; ++i) acc[ds][i] *= alpha;
-                m = mb;
+        for (int c = 0; c < kNb; ++c) {
+            sc[c] = use[c] ? row_score<T, D, G>(q, kr[c]) * p.scale_log2e : -INFINITY;
+            mb = fmaxf(mb, sc[c]);
+        }
+        if (mb == -INFINITY) return;
+        if constexpr (kApart) values();
+        if (mb > m + kRescaleSlack) {
+            const float alpha = __builtin_amdgcn_exp2f(m - mb);
+            l *= alpha;
+#pragma unroll
+            for (int i = 0; i < E; ++i) acc[i] *= alpha;
+            m = mb;
+        }
+#pragma unroll
+        for (int c = 0; c < kNb; ++c) {
+            const float pj = __builtin_amdgcn_exp2f(sc[c] - m);
+            l += pj;
+            if constexpr (CAUSAL) {
+#pragma unroll
+                for (int i = 0; i < CH; ++i) vr[c][i] = use[c] ? vr[c][i] : make_uint4(0u, 0u, 0u, 0u);
             }
-            batch(k0, [&](uint32_t off, float sc) {
-                const float pj = __builtin_amdgcn_exp2f(sc - m);
-                l += pj;
+            accumulate_row<T, CH>(acc, pj, vr[c]);
+        }
+    };
+    for (int e = 0; e < (MK > 1 ? p.kappa : 1); ++e) {
+        uint32_t u, v;
+        if constexpr (MULTI)
+            ws.centre(e, u, v);
+        else
+            divmod(static_cast<uint32_t>(clamp_index(p.J[g], p.nkeys)), p.div_wk, u, v);
+        uint32_t key[kNb];
+        bool use[kNb];
+        if constexpr (kRows) {
+            for (int r = max(static_cast<int>(u) - B, 0); r <= min(static_cast<int>(u) + B, p.Hk - 1); ++r) {
+                bool any = false;
 #pragma unroll
-                for (int ds = 0; ds < TR::kDs; ++ds) {
-                    const typename TR::Frag vr = TR::frag(Vb + off, ds, g4);
-#pragma unroll
-                    for (int i = 0; i < kE; ++i) acc[ds][i] = fmaf(pj, static_cast<float>(vr[i]), acc[ds][i]);
+                for (int c = 0; c < W; ++c) {
+                    const int col = static_cast<int>(v) + c - B, in = min(max(col, 0), p.Wk - 1);
+                    key[c] = static_cast<uint32_t>(r * p.Wk + in);
+                    use[c] = col == in;
+                    if constexpr (MULTI) use[c] = use[c] && !ws.skip(e, r, in);
+                    any = any || use[c];
                 }
-            });
+                if (any) batch(key, use);
+            }
+        } else {
+            const int r0 = max(static_cast<int>(u) - B, 0), r1 = min(static_cast<int>(u) + B, p.Hk - 1);
+            const int c0 = max(static_cast<int>(v) - B, 0), c1 = min(static_cast<int>(v) + B, p.Wk - 1);
+            int r = r0, c = c0;
+            while (r <= r1) {
+                bool any = false;
+#pragma unroll
+                for (int j = 0; j < kNb; ++j) {  // slots past the window's end read the match's row
+                    use[j] = r <= r1;
+                    key[j] = use[j] ? static_cast<uint32_t>(r * p.Wk + c) : u * p.Wk + v;
+                    if constexpr (MULTI) use[j] = use[j] && !ws.skip(e, r, c);
+                    any = any || use[j];
+                    const bool wrap = c == c1;
+                    c = wrap ? c0 : c + 1;
+                    r += wrap ? 1 : 0;
+                }
+                if (any) batch(key, use);
+            }
         }
     }
-    const float inv = l > 0.f ? 1.f / l : 0.f;
-    uint16_t* const orow = static_cast<uint16_t*>(p.out) + static_cast<size_t>(g) * D;
-#pragma unroll
-    for (int ds = 0; ds < TR::kDs; ++ds)
-#pragma unroll
-        for (int i = 0; i < kE; ++i)
-            orow[32 * ds + kE * g4 + i] = static_cast<uint16_t>(f32_to_bf16_rne(acc[ds][i] * inv));
+    store_row<T, D, G>(p.out, g, lane, acc, l > 0.f ? 1.f / l : 0.f);  // an empty set gives a zero row
+}
+
+// The queries of a wave's tile whose bits are set in `todo`.
+template <int D, int W, bool CAUSAL, int MK>
+__device__ __forceinline__ void attend_queries(const AttParams& p, uint32_t blk, int wave, int lane, uint32_t todo)
+{
+    constexpr int G = kQueryLanes<D>;
+    for (int i = lane / G; i < 16; i += 64 / G) {
+        uint32_t g;
+        if (((todo >> i) & 1u) && tile_item<kBlock / 4>(p.tq, blk, tile_wave_item(p.tq, wave, i), g))
+            attend_query<D, W, CAUSAL, MK>(p, g, lane & (G - 1));
+    }
 }
 
 // Waves per SIMD the registers are sized for: at d = 64 at most 96 VGPRs, five waves, hide more of the row
 // loads than four; the causal mask's registers and those of up to 4 windows do not fit there without spills,
 // so they take four, and up to 8 windows, or 4 with the causal mask, three; 128 channels double the
 // accumulators, the query's operands and the rows in flight.
-constexpr int tile_waves(int D, bool causal, int MK)
+constexpr int tile_waves(int D, int W, bool causal, int MK)
 {
-    if (D == 128) return causal || MK > 1 ? 2 : 3;
+    if (D == 128) return MK == 4 ? 2 : 3;
+    if (D == 16) return MK == 4 ? (causal ? 4 : 5) : MK == 2 ? 5 : 6;
+    if (D == 64 && W == 9) return MK == 4 && causal ? 3 : 4;
     return MK > 4 || (MK == 4 && causal) ? 3 : causal || MK > 1 ? 4 : 5;
 }
 
@@ -359,7 +412,7 @@ constexpr int tile_waves(int D, bool causal, int MK)
 constexpr bool full_weights(int D, int W) { return D == 16 || D == 128 || W == 9; }
 
 template <int D, int W, bool CAUSAL, int MK>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(tile_waves(D, CAUSAL, MK)))) void
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(tile_waves(D, W, CAUSAL, MK)))) void
 attend_tile_kernel(AttParams p)
 {
     using TR = TileRow<D>;
@@ -432,7 +485,7 @@ attend_tile_kernel(AttParams p)
             int iu = u, iv = v;
 #pragma unroll
             for (int e = 0; e < NW; ++e) iu = ew == e ? ju[e] : iu, iv = ew == e ? jv[e] : iv;
-            tc = tile_clusters_joint<B, NJ>(valid && ew < p.kappa, iu, iv, lane, rc, p.Hk, p.Wk);
+            tc = tile_clusters_joint<B, NJ, kFull>(valid && ew < p.kappa, iu, iv, lane, rc, p.Hk, p.Wk, p.tile_blocks);
 #pragma unroll
             for (int e = 0; e < NJ; ++e) jmine[e] = __shfl(tc.mine, m + 16 * e);
         }
@@ -450,9 +503,16 @@ attend_tile_kernel(AttParams p)
         }
         joint_round(0);
     } else {
-        tc = tile_clusters<B, CAUSAL>(valid, u, v, m, lane, rc, p.Hk, p.Wk, qx, qy);
+        tc = tile_clusters<B, CAUSAL, kFull>(valid, u, v, m, lane, rc, p.Hk, p.Wk, qx, qy, p.tile_blocks);
     }
     if (tc.nclu == 0) return;  // no query of this wave lies inside the grid
+    if constexpr (kFull) {
+        // matches that lie too far apart to share rows
+        if (tc.nclu < 0) {
+            attend_queries<D, W, CAUSAL, MK>(p, blk, wave, lane, 0xFFFFu);
+            return;
+        }
+    }
     int nclu = tc.nclu, mine = tc.mine, wr0 = tc.wr0, wrn = tc.wrn;
     uint32_t wcols = tc.wcols;
     // several windows: the centres of windows 0 .. e-1 of query m, as rows relative to window e's first
@@ -742,33 +802,32 @@ attend_tile_kernel(AttParams p)
         lt = lsum + __shfl_xor(lsum, 16);
         lt += __shfl_xor(lt, 32);
     }
-    if (!valid) return;
     // (two parts: a reciprocal within 1 ulp is far below their error)
     const float inv = lt > 0.f ? (kFull ? 1.f / lt : __builtin_amdgcn_rcpf(lt)) : 0.f;
+    uint32_t apart = 0u;  // bit m: query m's row is not stored here
     if constexpr (kFull) {
-        // A query's row is stored here or by attend_plain_row, never by
-        // both: their lanes hold different channels, and nothing would order the two stores
+        // a query whose sums are not finite (its row is then stored by attend_query alone, whose lanes hold other
+        // channels: nothing would order two stores)
         float t = lt;
 #pragma unroll
         for (int o = 0; o < kOt; ++o) t += (fabsf(acc[o][0]) + fabsf(acc[o][1])) + (fabsf(acc[o][2]) + fabsf(acc[o][3]));
         const uint64_t bad = __ballot(!(t < INFINITY));
-        const uint32_t of = static_cast<uint32_t>(bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xFFFFu;  // bit m: query m
-        if ((of >> m) & 1u) {
-            attend_plain_row<D, W, MK>(p, g, g4);
-            return;
+        apart = static_cast<uint32_t>(bad | bad >> 16 | bad >> 32 | bad >> 48) & 0xFFFFu;
+    }
+    if (valid && !((apart >> m) & 1u)) {
+        // lane holds channels 16 o + 4 g4 + i of query m; pairs rounded to bf16 (nearest even) together
+        uint16_t* const orow = static_cast<uint16_t*>(p.out) + static_cast<size_t>(g) * D;
+        auto bf2 = [](float a, float b) {
+            return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+        };
+#pragma unroll
+        for (int o = 0; o < kOt; ++o) {
+            const uint32_t w0 = bf2(acc[o][0] * inv, acc[o][1] * inv);
+            const uint32_t w1 = bf2(acc[o][2] * inv, acc[o][3] * inv);
+            *reinterpret_cast<uint2*>(orow + 16 * o + 4 * g4) = make_uint2(w0, w1);
         }
     }
-    // lane holds channels 16 o + 4 g4 + i of query m; pairs rounded to bf16 (nearest even) together
-    uint16_t* const orow = static_cast<uint16_t*>(p.out) + static_cast<size_t>(g) * D;
-    auto bf2 = [](float a, float b) {
-        return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
-    };
-#pragma unroll
-    for (int o = 0; o < kOt; ++o) {
-        const uint32_t w0 = bf2(acc[o][0] * inv, acc[o][1] * inv);
-        const uint32_t w1 = bf2(acc[o][2] * inv, acc[o][3] * inv);
-        *reinterpret_cast<uint2*>(orow + 16 * o + 4 * g4) = make_uint2(w0, w1);
-    }
+    if constexpr (kFull) attend_queries<D, W, CAUSAL, MK>(p, blk, wave, lane, apart);
 }
 
 template <typename T, int D, int MK>
@@ -795,10 +854,15 @@ hipError_t run_attend_m(const AttParams& p, int window, uint64_t blocks, hipStre
 // displaced by up to 24 px that vary over 8 px: 5 x 5 70 -> 53 us with 128
 // channels, 51 -> 45 with 16) and lose where they do not (one 400 x 300 slice,
 // displaced by up to 60 px that vary over 4 px, 5 % elsewhere: 73 -> 83 us and
-// 25 -> 30).  The others gain on both: 128 channels 7 x 7 120 -> 65 and 121 ->
-// 112 us, two 5 x 5 windows 90 -> 49 (97 x 111 x 8) and 129 -> 97; 16 channels
-// 7 x 7 95 -> 61 and 46 -> 38; 9 x 9 of 64 channels 202 -> 88 (256 x 256 x 4)
-// and 109 -> 75, of 32 63 -> 31 and 87 -> 54.
+// 25 -> 30).  The others gain where matches lie together (PatchMatch maps of
+// smooth images, 8 x 97 x 111: 128 channels 7 x 7 85 -> 50 us, two 5 x 5
+// windows 98 -> 64, two 9 x 9 251 -> 93; 16 channels 7 x 7 29 -> 22; 64
+// channels 9 x 9 74 -> 38), and keep the lane groups' time where they do not:
+// there a wave leaves the matrix cores (tile_blocks).  With 128 channels that
+// way takes a wave two rounds of 8 queries, which only a call that fills the
+// machine hides (two 5 x 5 windows, maps of noise: 4 x 64 x 64, one wave per
+// SIMD, 1.4 times the lane groups' time, 8 x 64 x 64 1.06), so smaller calls
+// stay on the lane groups.
 #ifndef SCRAM_ATTEND_TILE
 #define SCRAM_ATTEND_TILE 1
 #endif
@@ -815,9 +879,14 @@ hipError_t run_attend(const AttParams& p0, int window, hipStream_t st, hipEvent_
         const bool fits = kMid && window <= 7 ? p.kappa <= kMaxKappa : p.kappa <= 4;
         const bool pays = kMid || window > 5 || (D == 128 && window == 5 && p.kappa > 1);
         const uint64_t tiles = tiling_blocks(make_tiling(p.Hq, p.Wq, kBlock / 4), p.n / (static_cast<uint32_t>(p.Hq) * p.Wq));
-        if (tiles <= kMaxBlocks && fits && pays && window >= 3 && window <= 9 && p.scale_log2e > 0.f &&
+        constexpr uint64_t kFewTiles = D == 128 ? 512 : 1;  // (512: two waves per SIMD)
+        if (tiles >= kFewTiles && tiles <= kMaxBlocks && fits && pays && window >= 3 && window <= 9 && p.scale_log2e > 0.f &&
             static_cast<uint64_t>(p.nkeys) * (2 * D) <= 0xFFFFFFFFull) {
             p.tq = make_tiling(p.Hq, p.Wq, kBlock / 4);
+            // a wave's windows hold kappa w^2 blocks of 16 keys; up to 5/8 of that many in its boxes the matrix cores
+            // are faster than the lane groups (limits of a quarter to all of it tried on smooth images' maps and on
+            // noise: flat for the former from a half on, for the latter rising from three quarters on)
+            p.tile_blocks = p.kappa * window * window * 5 / 8;
             auto go = [&](auto w) {
                 constexpr int Wn = decltype(w)::value;
                 // the smallest bound on the windows per query that holds this call's

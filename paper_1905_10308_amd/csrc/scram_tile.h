@@ -166,16 +166,28 @@ struct TileClusters {
     uint32_t wcols, wcut;
 };
 
+// Blocks of 16 keys in the box of the centres in rows ulo .. uhi, columns vlo .. vhi; wave-uniform, lane 0's rows
+// and columns.
+template <int B>
+__device__ __forceinline__ int tile_box_blocks(int ulo, int uhi, int vlo, int vhi, int Hk, int Wk)
+{
+    ulo = __builtin_amdgcn_readfirstlane(ulo), uhi = __builtin_amdgcn_readfirstlane(uhi);
+    vlo = __builtin_amdgcn_readfirstlane(vlo), vhi = __builtin_amdgcn_readfirstlane(vhi);
+    const int h = min(uhi + B, Hk - 1) - max(ulo - B, 0) + 1, w = min(vhi + B, Wk - 1) - max(vlo - B, 0) + 1;
+    return (h * w + 15) >> 4;
+}
+
 // Clusters of the 16 centres (u, v) of a wave (windows of half side B, key
 // grid Hk x Wk, cluster radius rc); CAUSAL: the query sits at (qx, qy) of the
-// same grid.  nclu == 0 when no query of the wave is valid.
-template <int B, bool CAUSAL = false>
+// same grid.  nclu == 0 when no query of the wave is valid; BOUNDED: nclu < 0 when the boxes hold more than
+// `most` blocks of 16 keys (the rest is then not set).
+template <int B, bool CAUSAL = false, bool BOUNDED = false>
 __device__ __forceinline__ TileClusters tile_clusters(bool valid, int u, int v, int m, int lane, int rc, int Hk,
-                                                      int Wk, int qx = 0, int qy = 0)
+                                                      int Wk, int qx = 0, int qy = 0, int most = 0)
 {
     TileClusters tc;
     int t_r0 = 0, t_c0 = 0, t_bw = 1, t_h = 0;
-    int nclu = 0, mine = -1;
+    int nclu = 0, mine = -1, blocks = 0;
     uint32_t todo = static_cast<uint32_t>(__ballot(valid)) & 0xFFFFu;  // bit m: query m (lanes 16.. repeat 0..15)
     while (todo) {
         const int a = __builtin_ctz(todo);
@@ -192,6 +204,13 @@ __device__ __forceinline__ TileClusters tile_clusters(bool valid, int u, int v, 
         t_h = here ? min(uhi + B, Hk - 1) - max(ulo - B, 0) + 1 : t_h;
         t_bw = here ? min(vhi + B, Wk - 1) - max(vlo - B, 0) + 1 : t_bw;
         ++nclu;
+        if constexpr (BOUNDED) {
+            blocks += tile_box_blocks<B>(ulo, uhi, vlo, vhi, Hk, Wk);
+            if (blocks > most) {
+                tc.nclu = -1;
+                return tc;
+            }
+        }
     }
     tc.t_r0 = t_r0, tc.t_c0 = t_c0, tc.t_bw = t_bw, tc.t_h = t_h, tc.nclu = nclu, tc.mine = mine;
     // the rest of each cluster's scalars, once for all clusters
@@ -224,15 +243,15 @@ __device__ __forceinline__ TileClusters tile_clusters(bool valid, int u, int v, 
 // (window i / 16 of query i mod 16), the other lanes repeat them; valid is false for a centre that
 // does not exist; mine is the cluster of the lane's centre.  Only the clusters' scalars are set (the
 // caller places each window in its own box).
-template <int B, int NJ>
+template <int B, int NJ, bool BOUNDED = false>
 __device__ __forceinline__ TileClusters tile_clusters_joint(bool valid, int u, int v, int lane, int rc, int Hk,
-                                                            int Wk)
+                                                            int Wk, int most = 0)
 {
     static_assert(NJ == 2 || NJ == 4, "16 NJ centres in the lanes of a wave");
     constexpr uint64_t kItems = NJ == 4 ? ~0ull : 0xFFFFFFFFull;
     TileClusters tc;
     int t_r0 = 0, t_c0 = 0, t_bw = 1, t_h = 0;
-    int nclu = 0, mine = -1;
+    int nclu = 0, mine = -1, blocks = 0;
     const int it = lane & (16 * NJ - 1);
     uint64_t todo = static_cast<uint64_t>(__ballot(valid)) & kItems;  // bit i: centre i
     while (todo) {
@@ -257,6 +276,13 @@ __device__ __forceinline__ TileClusters tile_clusters_joint(bool valid, int u, i
         t_h = here ? min(uhi + B, Hk - 1) - max(ulo - B, 0) + 1 : t_h;
         t_bw = here ? min(vhi + B, Wk - 1) - max(vlo - B, 0) + 1 : t_bw;
         ++nclu;
+        if constexpr (BOUNDED) {
+            blocks += tile_box_blocks<B>(ulo, uhi, vlo, vhi, Hk, Wk);
+            if (blocks > most) {
+                tc.nclu = -1;
+                return tc;
+            }
+        }
     }
     tc.t_r0 = t_r0, tc.t_c0 = t_c0, tc.t_bw = t_bw, tc.t_h = t_h, tc.nclu = nclu, tc.mine = mine;
     tc.t_inv = __builtin_amdgcn_rcpf(static_cast<float>(t_bw));

@@ -9,10 +9,24 @@ from gpu_util import TOL, row_rel_err, tile_maps, to_dev
 
 pytestmark = pytest.mark.gpu
 
-# 16 and 128 channels take the matrix cores from 7 x 7 on, 128 also with several 5 x 5 windows, 32 and 64 with 9 x 9 too
-SHAPES = [(16, 5), (16, 7), (16, 9), (32, 9), (64, 9), (128, 3), (128, 5), (128, 9)]
-# several tiles with ragged edges, the smallest grids, one row, one column, two grids
-GRIDS = [(2, 21, 37, 21, 37), (1, 3, 5, 3, 5), (1, 1, 50, 1, 50), (1, 50, 1, 50, 1), (1, 19, 11, 33, 30)]
+# 16 and 128 channels take the matrix cores from 7 x 7 on, 128 also with several 5 x 5 windows, 32 and 64 with 9 x 9 too;
+# (16, 5), (128, 3) and (128, 5) with one map take the lane-group kernels: controls
+SHAPES = [(16, 5), (16, 7), (16, 9), (32, 9), (64, 9), (128, 3), (128, 5), (128, 7), (128, 9)]
+# several tiles with ragged edges, the smallest grids, one row, one column, two grids, and a grid on which a wave's
+# random matches lie too far apart for the matrix cores
+GRIDS = [(2, 21, 37, 21, 37), (1, 3, 5, 3, 5), (1, 1, 50, 1, 50), (1, 50, 1, 50, 1), (1, 19, 11, 33, 30),
+         (1, 40, 61, 40, 61)]
+
+
+def attend(scram, Q, K, V, J, window, scale=None, causal=False):
+    """``sparse_attend`` of slices in numpy; with 128 channels of 512 copies of them, so that the call is wide enough
+    for the matrix cores, every copy with the same bits."""
+    n, S = (512 if Q.shape[-1] == 128 else 1), Q.shape[0]
+    dev = [to_dev(x, "bf16").repeat(n, 1, 1, 1) for x in (Q, K, V)]
+    Jd = torch.from_numpy(np.ascontiguousarray(J)).cuda().repeat(1, n, 1, 1)
+    got = scram.sparse_attend(*dev, Jd, window, scale, causal=causal)
+    assert (got.view(torch.int16).reshape(n, -1) == got[:S].view(torch.int16).reshape(1, -1)).all()
+    return got[:S]
 
 
 @pytest.mark.parametrize("d,window", SHAPES)
@@ -22,13 +36,12 @@ def test_attend_widths(scram, d, window, grid):
     rng = np.random.default_rng(d + window + Hq)
     Q, K, V = (synth._round_bf16(rng.standard_normal(s).astype(np.float32)) for s in
                ((S, Hq, Wq, d), (S, Hk, Wk, d), (S, Hk, Wk, d)))
-    Qd, Kd, Vd = (to_dev(x, "bf16") for x in (Q, K, V))
     m = tile_maps(S, Hq, Wq, Hk, Wk, rng)
     sets = [m[n][None] for n in ("random", "coherent", "lattice7", "lattice10", "two_far", "outliers")]
     sets += [np.stack([m["coherent"], m["outliers"]]), np.stack([m["random"], m["coherent"], m["corner_last"]])]
     for J in sets:
         for causal in ((False, True) if (Hq, Wq) == (Hk, Wk) else (False,)):
-            got = scram.sparse_attend(Qd, Kd, Vd, torch.from_numpy(J).cuda(), window, causal=causal)
+            got = attend(scram, Q, K, V, J, window, causal=causal)
             ref = oracle.sparse_attend(Q, K, V, J, window, d ** -0.5, flags=oracle.CAUSAL if causal else 0)
             err = row_rel_err(got.double().cpu().numpy(), ref)
             assert err.max() <= TOL["bf16"], (J.shape[0], causal, err.max())
@@ -44,11 +57,11 @@ def test_non_finite_values_stay_in_their_windows(scram, d, window):
     rng = np.random.default_rng(d + window)
     Q, K, V = (synth._round_bf16(rng.standard_normal((S, H, W, d)).astype(np.float32)) for _ in range(3))
     J = np.stack([np.arange(H * W).reshape(S, H, W), rng.integers(0, H * W, (S, H, W))]).astype(np.int32)
-    clean = scram.sparse_attend(*(to_dev(x, "bf16") for x in (Q, K, V)), torch.from_numpy(J).cuda(), window)
+    clean = attend(scram, Q, K, V, J, window)
     bad = [(7, 9), (20, 3)]
     V[0, 7, 9, d // 2] = np.inf
     V[0, 20, 3, 1] = np.nan
-    got = scram.sparse_attend(*(to_dev(x, "bf16") for x in (Q, K, V)), torch.from_numpy(J).cuda(), window)
+    got = attend(scram, Q, K, V, J, window)
     near = np.zeros((S, H, W), bool)
     for u, v in bad:
         for m in J:
@@ -86,12 +99,11 @@ def test_non_finite_values_stay_in_their_channels(scram, d, window, kappa, causa
     """Of a query whose set holds a value row with an infinity or a NaN in one channel, that channel is not
     finite and every other one holds what it held: a row has one writer."""
     H, W, Q, K, V, J = unit_case(d, kappa, d + window + kappa)
-    Jd, dev = torch.from_numpy(J).cuda(), [to_dev(x, "bf16") for x in (Q, K, V)]
-    clean = scram.sparse_attend(*dev, Jd, window, causal=causal).float().cpu().numpy().reshape(H * W, d)
+    clean = attend(scram, Q, K, V, J, window, causal=causal).float().cpu().numpy().reshape(H * W, d)
     bad = {7 * W + 9: (d // 2, np.inf), 3 * W + 3: (1, np.nan), 12 * W + 20: (d - 1, -np.inf)}
     for k, (ch, x) in bad.items():
         V[0, k // W, k % W, ch] = x
-    got = scram.sparse_attend(dev[0], dev[1], to_dev(V, "bf16"), Jd, window, causal=causal)
+    got = attend(scram, Q, K, V, J, window, causal=causal)
     got = got.float().cpu().numpy().reshape(H * W, d)
     held = key_sets(J, H, W, window, causal)
     off = np.zeros((H * W, d), bool)
@@ -146,7 +158,7 @@ def test_scores_that_are_not_finite(scram, d, window, kappa, causal):
     K[0, 0, 0, 1] = K[0, 9, 13, d - 1] = np.nan
     K[0, 15, 6, d // 2] = np.inf
     Q[0, 20, 20] = np.nan
-    got = scram.sparse_attend(*(to_dev(x, "bf16") for x in (Q, K, V)), torch.from_numpy(J).cuda(), window, causal=causal)
+    got = attend(scram, Q, K, V, J, window, causal=causal)
     got = got.double().cpu().numpy().reshape(H * W, d)
     Qf, Kf, Vf = (x.astype(np.float64).reshape(H * W, d) for x in (Q, K, V))
     with np.errstate(invalid="ignore"):
@@ -194,10 +206,9 @@ def test_weights_keep_24_bits(scram, d, window, kappa):
     Q[..., 0] = 1.0
     t = np.arange(H * W) % (n * n)
     J = np.broadcast_to(centre[t].reshape(1, 1, H, W), (kappa, 1, H, W)).astype(np.int32)
-    dev = [to_dev(a, "bf16") for a in (Q, K, V)]
-    for a, b in zip(dev, (Q, K, V)):
-        assert np.array_equal(a.float().cpu().numpy(), b)  # (exact in bf16)
-    got = scram.sparse_attend(*dev, torch.from_numpy(np.ascontiguousarray(J)).cuda(), window, scale)
+    for a in (Q, K, V):
+        assert np.array_equal(synth._round_bf16(a), a)  # (exact in bf16)
+    got = attend(scram, Q, K, V, J, window, scale)
     got = got.double().cpu().numpy().reshape(H * W, d)
     sharp = (want > 32 * ulp)[t]
     assert sharp.sum() >= H * W // 4
