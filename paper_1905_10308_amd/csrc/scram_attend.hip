@@ -869,43 +869,65 @@ hipError_t run_attend_m(const AttParams& p, int window, uint64_t blocks, hipStre
 template <typename T, int D>
 constexpr bool kTileKernel = SCRAM_ATTEND_TILE && std::is_same<T, uint16_t>::value;
 
+// Fewest and most maps with which it takes windows of side W (most: 0, none).
+struct TileMaps {
+    int least, most;
+};
+constexpr TileMaps tile_maps(int D, int W)
+{
+    const bool mid = D == 32 || D == 64;
+    if (W < 3 || W > 9) return {1, 0};
+    if (mid) return {1, W <= 7 ? kMaxKappa : 4};
+    if (W > 5) return {1, 4};
+    return D == 128 && W == 5 ? TileMaps{2, 4} : TileMaps{1, 0};
+}
+
+// Windows of side W on the matrix cores, if they take this call; false: not launched.
+template <int D, int W>
+bool run_attend_tiles(const AttParams& p0, hipStream_t st, hipEvent_t e0, hipEvent_t e1, hipError_t& err)
+{
+    constexpr TileMaps kMaps = tile_maps(D, W);
+    if constexpr (kMaps.most == 0) {
+        return false;
+    } else {
+        constexpr uint64_t kFewTiles = D == 128 ? 512 : 1;  // (512: two waves per SIMD)
+        AttParams p = p0;
+        p.tq = make_tiling(p.Hq, p.Wq, kBlock / 4);
+        const uint64_t tiles = tiling_blocks(p.tq, p.n / p.tq.plane);
+        if (tiles < kFewTiles || tiles > kMaxBlocks || p.kappa < kMaps.least || p.kappa > kMaps.most) return false;
+        // a wave's windows hold kappa w^2 blocks of 16 keys; up to 5/8 of that many in its boxes the matrix cores
+        // are faster than the lane groups (limits of a quarter to all of it tried on smooth images' maps and on
+        // noise: flat for the former from a half on, for the latter rising from three quarters on)
+        p.tile_blocks = p.kappa * W * W * 5 / 8;
+        // the smallest bound on the windows per query that holds this call's
+        auto with = [&](auto mk) {
+            constexpr int MK = decltype(mk)::value;
+            err = p.causal ? launch(attend_tile_kernel<D, W, true, MK>, tiles, st, e0, e1, p)
+                           : launch(attend_tile_kernel<D, W, false, MK>, tiles, st, e0, e1, p);
+            return true;
+        };
+        if constexpr (kMaps.most > 4)
+            if (p.kappa > 4) return with(std::integral_constant<int, kMaxKappa>{});
+        if constexpr (kMaps.least == 1)
+            if (p.kappa == 1) return with(std::integral_constant<int, 1>{});
+        return p.kappa == 2 ? with(std::integral_constant<int, 2>{}) : with(std::integral_constant<int, 4>{});
+    }
+}
+
 template <typename T, int D>
 hipError_t run_attend(const AttParams& p0, int window, hipStream_t st, hipEvent_t e0, hipEvent_t e1)
 {
     constexpr int G = Lanes<T, D>::kAttend;
     AttParams p = p0;
     if constexpr (kTileKernel<T, D>) {
-        constexpr bool kMid = D == 32 || D == 64;
-        const bool fits = kMid && window <= 7 ? p.kappa <= kMaxKappa : p.kappa <= 4;
-        const bool pays = kMid || window > 5 || (D == 128 && window == 5 && p.kappa > 1);
-        const uint64_t tiles = tiling_blocks(make_tiling(p.Hq, p.Wq, kBlock / 4), p.n / (static_cast<uint32_t>(p.Hq) * p.Wq));
-        constexpr uint64_t kFewTiles = D == 128 ? 512 : 1;  // (512: two waves per SIMD)
-        if (tiles >= kFewTiles && tiles <= kMaxBlocks && fits && pays && window >= 3 && window <= 9 && p.scale_log2e > 0.f &&
-            static_cast<uint64_t>(p.nkeys) * (2 * D) <= 0xFFFFFFFFull) {
-            p.tq = make_tiling(p.Hq, p.Wq, kBlock / 4);
-            // a wave's windows hold kappa w^2 blocks of 16 keys; up to 5/8 of that many in its boxes the matrix cores
-            // are faster than the lane groups (limits of a quarter to all of it tried on smooth images' maps and on
-            // noise: flat for the former from a half on, for the latter rising from three quarters on)
-            p.tile_blocks = p.kappa * window * window * 5 / 8;
-            auto go = [&](auto w) {
-                constexpr int Wn = decltype(w)::value;
-                // the smallest bound on the windows per query that holds this call's
-                auto with = [&](auto mk) {
-                    constexpr int MK = decltype(mk)::value;
-                    return p.causal ? launch(attend_tile_kernel<D, Wn, true, MK>, tiles, st, e0, e1, p)
-                                    : launch(attend_tile_kernel<D, Wn, false, MK>, tiles, st, e0, e1, p);
-                };
-                if constexpr ((D == 32 || D == 64) && Wn <= 7) {
-                    if (p.kappa > 4) return with(std::integral_constant<int, kMaxKappa>{});
-                }
-                return p.kappa == 1   ? with(std::integral_constant<int, 1>{})
-                       : p.kappa == 2 ? with(std::integral_constant<int, 2>{})
-                                      : with(std::integral_constant<int, 4>{});
-            };
-            return window == 3   ? go(std::integral_constant<int, 3>{})
-                   : window == 5 ? go(std::integral_constant<int, 5>{})
-                   : window == 7 ? go(std::integral_constant<int, 7>{})
-                                 : go(std::integral_constant<int, 9>{});
+        if (p.scale_log2e > 0.f && static_cast<uint64_t>(p.nkeys) * (2 * D) <= 0xFFFFFFFFull) {
+            hipError_t err = hipSuccess;
+            const bool ran = window == 3   ? run_attend_tiles<D, 3>(p, st, e0, e1, err)
+                             : window == 5 ? run_attend_tiles<D, 5>(p, st, e0, e1, err)
+                             : window == 7 ? run_attend_tiles<D, 7>(p, st, e0, e1, err)
+                             : window == 9 ? run_attend_tiles<D, 9>(p, st, e0, e1, err)
+                                           : false;
+            if (ran) return err;
         }
     }
     p.tq = make_tiling(p.Hq, p.Wq, Row<T, D, G>::kQpb, kLaneSkew);
