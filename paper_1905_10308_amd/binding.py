@@ -191,13 +191,15 @@ def _pad_channels(width: int, *tensors):
 
     Zero channels add exact zeros to every dot product, so scores, weights and outputs in the original
     channels are unchanged; the softmax scale is taken from the original width."""
-    short = [t for t in tensors if t.shape[-1] < width and t.numel()]
-    if not short or width not in NATIVE_WIDTHS:  # (a width the library rejects)
+    if width not in NATIVE_WIDTHS:  # (a width the library rejects)
         return tensors
-    padded = [t.new_empty(tuple(t.shape[:-1]) + (width,)) for t in short]
-    _resize_channels(short, padded, [t.shape[-1] for t in short], width, False)
-    found = iter(padded)
-    return tuple(next(found) if t.shape[-1] < width and t.numel() else t for t in tensors)
+    # a tensor without elements (no channels, say) has nothing to copy
+    wide = [t if t.shape[-1] == width else (t.new_empty if t.numel() else t.new_zeros)(tuple(t.shape[:-1]) + (width,))
+            for t in tensors]
+    short = [(t, p) for t, p in zip(tensors, wide) if p is not t and t.numel()]
+    if short:
+        _resize_channels([t for t, _ in short], [p for _, p in short], [t.shape[-1] for t, _ in short], width, False)
+    return tuple(wide)
 
 
 def _unpad_into(res, width: int, out=None):
@@ -209,18 +211,18 @@ def _unpad_into(res, width: int, out=None):
         return res
     if out is None:
         out = res.new_empty(tuple(res.shape[:-1]) + (width,))
-    _resize_channels([res], [out], [width], res.shape[-1], True)
+    if out.numel():
+        _resize_channels([res], [out], [width], res.shape[-1], True)
     return out
 
 
 def _unpad(width: int, *pairs):
     """For each (tensor of ``width`` channels, n): its first n channels, in one launch."""
-    short = [(t, n) for t, n in pairs if n < width]
-    cut = [t.new_empty(tuple(t.shape[:-1]) + (n,)) for t, n in short]
+    cut = [t if n == width else t.new_empty(tuple(t.shape[:-1]) + (n,)) for t, n in pairs]
+    short = [(t, c, n) for (t, n), c in zip(pairs, cut) if c is not t and c.numel()]
     if short:
-        _resize_channels([t for t, _ in short], cut, [n for _, n in short], width, True)
-    found = iter(cut)
-    return tuple(next(found) if n < width else t for t, n in pairs)
+        _resize_channels([t for t, _, _ in short], [c for _, c, _ in short], [n for _, _, n in short], width, True)
+    return tuple(cut)
 
 
 def _raw_stream(device):

@@ -45,3 +45,38 @@ def test_pad_and_cut(scram, dtype, rows, n, width):
     cx, cy = binding._unpad(width, (px, n), (y, width))
     assert cy is y and torch.equal(cx, x)
     assert torch.equal(binding._unpad_into(y, n), y[..., :n])
+
+
+def test_tensors_without_elements():
+    """No channels pad to zeros, no rows to no rows, and zero channels of a wide tensor are an empty one: nothing of
+    it needs the library."""
+    none, row = torch.empty(2, 3, 4, 0), torch.empty(0, 3, 4, 5)
+    a, b = binding._pad_channels(16, none, row)
+    assert a.shape == (2, 3, 4, 16) and not a.any() and b.shape == (0, 3, 4, 16)
+    wide = torch.ones(2, 3, 4, 16)
+    assert binding._unpad_into(wide, 0).shape == (2, 3, 4, 0)
+    out = torch.empty(2, 3, 4, 0)
+    assert binding._unpad_into(wide, 0, out) is out
+    c, d = binding._unpad(16, (wide, 0), (wide, 16))
+    assert c.shape == (2, 3, 4, 0) and d is wide
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_calls_without_channels(scram, dtype):
+    """Queries and keys of no channels score 0 everywhere, values of none give rows of none."""
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    Q, K, V = (torch.randn(2, 9, 11, 3, device="cuda", generator=gen).to(dtype) for _ in range(3))
+    none = Q[..., :0].contiguous()
+    J, s = scram.patchmatch(none, none, 2, 7, return_score=True)
+    assert not s.any() and ((J >= 0) & (J < 99)).all()
+    assert torch.equal(scram.patchmatch_kappa(none, none, 1, 2, 7)[0], J)
+    # every key of the window has the same weight
+    got, want = (scram.sparse_attend(q, k, V, J, 3, 1.0) for q, k in ((none, none), (Q * 0, K)))
+    assert torch.equal(got, want)
+    assert scram.sparse_attend(Q, K, none, J, 3).shape == (2, 9, 11, 0)
+    assert scram.snis_attend(Q, K, none, J, 8).shape == (2, 9, 11, 0)
+    dQ, dK, dV = scram.sparse_attend_backward(Q, K, none, J, none, 3)
+    assert not dQ.any() and not dK.any() and dV.shape == (2, 9, 11, 0)
+    dQ, dK, dV = scram.sparse_attend_backward(none, none, V, J, V, 3, 1.0)
+    assert dQ.shape == dK.shape == (2, 9, 11, 0) and dV.shape == V.shape and dV.any()
