@@ -331,10 +331,11 @@ def _patchmatch(noalloc, Q, K, iters, seed, init, init_score, t0, flags, prev, s
             prev = None
     if causal:
         flags |= CAUSAL
+    code = _dtype_code(Q)
     d = _native_width(d)
     Q, K = _pad_channels(d, Q, K)
     ev = None if events is None else _event_array(events, 2 * (int(iters) + 1))
-    args = (_ptr(Q), _ptr(K), _dtype_code(Q), S, Hq, Wq, Hk, Wk, d, int(iters), int(seed) & 0xFFFFFFFFFFFFFFFF,
+    args = (_ptr(Q), _ptr(K), code, S, Hq, Wq, Hk, Wk, d, int(iters), int(seed) & 0xFFFFFFFFFFFFFFFF,
             _ptr(init), _ptr(init_score), int(t0), int(flags), _ptr(prev), int(n_prev), int(sep), _ptr(out),
             _ptr(score_out))
     if noalloc:
@@ -376,12 +377,13 @@ def sparse_attend(Q, K, V, argmax, window: int, scale: float | None = None, *, c
     _same_device(dev, K=K, V=V, argmax=argmax, out=out)
     if out is not None:
         _check_buffer(out, "out", (S, Hq, Wq, dv), Q.dtype)
+    code = _dtype_code(Q)
     w = _native_width(max(d, dv))
     Q, K, V = _pad_channels(w, Q, K, V)
     res = out if out is not None and w == dv else torch.empty((S, Hq, Wq, w), dtype=Q.dtype, device=dev)
     ev = None if events is None else _event_array(events, 2)
     _call(lib().scram_sparse_attend, "scram_sparse_attend", dev,
-          (_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(argmax), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(window),
+          (_ptr(Q), _ptr(K), _ptr(V), code, _ptr(argmax), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(window),
            float(scale), CAUSAL if causal else 0, _ptr(res), ev))
     return _unpad_into(res, dv, out)
 
@@ -415,6 +417,7 @@ def sparse_attend_backward(Q, K, V, argmax, dO, window: int, scale: float | None
         scale = d ** -0.5
     dev = Q.device
     _same_device(dev, K=K, V=V, argmax=argmax, dO=dO, workspace=workspace)
+    code = _dtype_code(Q)
     w = _native_width(max(d, dv))
     dQ = torch.empty((S, Hq, Wq, w), dtype=torch.float32, device=dev)
     dK = torch.empty((S, Hk, Wk, w), dtype=torch.float32, device=dev)
@@ -424,7 +427,7 @@ def sparse_attend_backward(Q, K, V, argmax, dO, window: int, scale: float | None
     workspace = _workspace(workspace, need, dev)
     ev = None if events is None else _event_array(events, 6)
     _call(lib().scram_sparse_attend_backward, "scram_sparse_attend_backward", dev,
-          (_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(argmax), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(window),
+          (_ptr(Q), _ptr(K), _ptr(V), code, _ptr(argmax), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(window),
            float(scale), CAUSAL if causal else 0, _ptr(dO), _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(workspace),
            workspace.numel() * workspace.element_size(), ev))
     return _unpad(w, (dQ, d), (dK, d), (dV, dv))
@@ -467,6 +470,7 @@ def snis_attend(Q, K, V, modes, samples: int, *, alpha: float = 0.9, radius: int
     _same_device(dev, K=K, V=V, modes=modes, out=out)
     if out is not None:
         _check_buffer(out, "out", (S, Hq, Wq, dv), Q.dtype)
+    code = _dtype_code(Q)
     w = _native_width(max(d, dv))
     Q, K, V = _pad_channels(w, Q, K, V)
     res = out if out is not None and w == dv else torch.empty((S, Hq, Wq, w), dtype=Q.dtype, device=dev)
@@ -474,7 +478,7 @@ def snis_attend(Q, K, V, modes, samples: int, *, alpha: float = 0.9, radius: int
     var_t = torch.empty((S, Hq, Wq, w), dtype=torch.float32, device=dev) if var else None
     ev = None if events is None else _event_array(events, 2)
     _call(lib().scram_snis_attend, "scram_snis_attend", dev,
-          (_ptr(Q), _ptr(K), _ptr(V), _dtype_code(Q), _ptr(modes), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(samples),
+          (_ptr(Q), _ptr(K), _ptr(V), code, _ptr(modes), int(kappa), S, Hq, Wq, Hk, Wk, w, w, int(samples),
            float(alpha), int(radius), float(scale), int(seed) & 0xFFFFFFFFFFFFFFFF, CAUSAL if causal else 0, _ptr(res),
            _ptr(ess_t), _ptr(var_t), ev))
     out = _unpad_into(res, dv, out)
@@ -495,9 +499,10 @@ def patchmatch_kappa(Q, K, kappa: int, iters: int, seed: int, *, sep: int = 1, c
     dev = Q.device
     maps = torch.empty((kappa, S, Hq, Wq), dtype=torch.int32, device=dev)
     ws = torch.empty(max(patchmatch_workspace_bytes(S, Hq, Wq), 1), dtype=torch.uint8, device=dev)
+    code = _dtype_code(Q)
     d = _native_width(d)
     Q, K = _pad_channels(d, Q, K)
-    head = (_ptr(Q), _ptr(K), _dtype_code(Q), S, Hq, Wq, Hk, Wk, d, int(iters), int(seed) & 0xFFFFFFFFFFFFFFFF, None,
+    head = (_ptr(Q), _ptr(K), code, S, Hq, Wq, Hk, Wk, d, int(iters), int(seed) & 0xFFFFFFFFFFFFFFFF, None,
             None, 1, int(flags) | (CAUSAL if causal else 0))
     base, step, ws_ptr, ws_bytes = maps.data_ptr(), 4 * S * Hq * Wq, _ptr(ws), ws.numel()
     for c in range(kappa):  # run c reads the maps of runs 0 .. c - 1

@@ -80,3 +80,17 @@ def test_calls_without_channels(scram, dtype):
     assert not dQ.any() and not dK.any() and dV.shape == (2, 9, 11, 0)
     dQ, dK, dV = scram.sparse_attend_backward(none, none, V, J, V, 3, 1.0)
     assert dQ.shape == dK.shape == (2, 9, 11, 0) and dV.shape == V.shape and dV.any()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float16, torch.int32])
+def test_other_types_are_refused_as_such(scram, dtype):
+    """Also where rows of 8-byte elements would have to be padded first: a TypeError, as for widths that need none."""
+    Q = torch.zeros(1, 4, 5, 3, device="cuda", dtype=dtype)
+    J = torch.zeros(1, 4, 5, device="cuda", dtype=torch.int32)
+    for call in (lambda: scram.patchmatch(Q, Q, 1, 0), lambda: scram.patchmatch_kappa(Q, Q, 2, 1, 0),
+                 lambda: scram.patchmatch_noalloc(Q, Q, 1, 0), lambda: scram.sparse_attend(Q, Q, Q, J, 3),
+                 lambda: scram.sparse_attend_backward(Q, Q, Q, J, Q, 3), lambda: scram.snis_attend(Q, Q, Q, J, 4),
+                 lambda: scram.forward(Q, Q, Q, 1, 0, 3)):
+        with pytest.raises(TypeError):
+            call()
