@@ -1040,6 +1040,28 @@ bwd_key_strip_kernel(BwdParams p)
 // ---------------------------------------------------------------------------
 constexpr int kStripFE = 16;  // entries per chunk
 
+// Whether the causal mask leaves query qg (raster index `local`) one key in the union of its windows, at most one in the
+// window around (mu, mv) among them.  With b >= 1 and more than one key only the mask does.
+__device__ __forceinline__ bool one_key_left(const BwdParams& p, uint32_t qg, uint32_t local, int mu, int mv)
+{
+    // the window's first two keys in raster order
+    auto two = [&](int u, int v, uint32_t& first, uint32_t& second) {
+        const int r0 = max(u - p.b, 0), c0 = max(v - p.b, 0);
+        first = static_cast<uint32_t>(r0) * p.Wk + c0;
+        second = c0 < min(v + p.b, p.Wk - 1) ? first + 1 : r0 < min(u + p.b, p.Hk - 1) ? first + p.Wk : 0xFFFFFFFFu;
+    };
+    uint32_t first, second;
+    two(mu, mv, first, second);
+    if (first > local || second <= local) return false;
+    for (int f = 0; f < p.kappa; ++f) {  // (rarely reached)
+        uint32_t fu, fv, one, other;
+        divmod(static_cast<uint32_t>(clamp_index(p.J[static_cast<size_t>(f) * p.n + qg], p.nkeys)), p.div_wk, fu, fv);
+        two(static_cast<int>(fu), static_cast<int>(fv), one, other);
+        if (one <= local && (one != first || other <= local)) return false;
+    }
+    return true;
+}
+
 // The rows of gradients of key (kx, ky), entry by entry, by one wave: what the
 // lane-group kernels compute.  The strip kernel takes it for the keys whose
 // results are not finite, since a non-finite entry row reaches every key of
@@ -1067,6 +1089,8 @@ __device__ void key_grads_plain(const BwdParams& p, uint32_t s, int kx, int ky, 
             divmod(static_cast<uint32_t>(p.entries[x]), p.div_n, e, g);
             divmod(g, p.div_plane, sl, rem);
             bool ok = !p.causal || static_cast<uint32_t>(kx) * p.Wk + ky <= rem;
+            uint32_t mu, mv;
+            divmod(static_cast<uint32_t>(clamp_index(p.J[p.entries[x]], p.nkeys)), p.div_wk, mu, mv);
             for (int f = 0; f < static_cast<int>(e) && ok; ++f) {
                 uint32_t fu, fv;
                 divmod(static_cast<uint32_t>(clamp_index(p.J[static_cast<size_t>(f) * p.n + g], p.nkeys)), p.div_wk,
@@ -1088,7 +1112,9 @@ __device__ void key_grads_plain(const BwdParams& p, uint32_t s, int kx, int ky, 
                 dp += __shfl_xor(dp, m);
             }
             const float pr = __builtin_amdgcn_exp2f(sc * p.scale_log2e - p.lse2[g]);
-            const float ds = pr * (dp - p.Dq[g]);
+            // (a set of one key: D is this dp, summed in another order)
+            const bool one = p.causal && one_key_left(p, g, rem, static_cast<int>(mu), static_cast<int>(mv));
+            const float ds = pr * (dp - (one ? dp : p.Dq[g]));
 #pragma unroll
             for (int c = 0; c < kC; ++c) {
                 dk[c] = fmaf(ds, q[c], dk[c]);
@@ -1298,18 +1324,22 @@ bwd_key_strip_f32_kernel(BwdParams p)
             *reinterpret_cast<f32x4_t*>(s_q + (er + kRpi * j) * kRowF + 4 * ep) = rq[j];
             *reinterpret_cast<f32x4_t*>(s_g + (er + kRpi * j) * kRowF + 4 * ep) = rg[j];
         }
+        bool one = false;  // a query whose set is one key
         if (g4 == 0) {
             int4 meta = make_int4(-(1 << 30), -(1 << 30), 0, 0);  // no key is near this match
             if constexpr (kQueryIndex) s_el[m][0] = s_el[m][1] = 0;
             if (code >= 0) {
                 uint32_t mu, mv;
                 divmod(static_cast<uint32_t>(clamp_index(match, p.nkeys)), p.div_wk, mu, mv);
-                meta = make_int4(static_cast<int>(mu), static_cast<int>(mv), __float_as_int(lse), __float_as_int(dq));
                 if constexpr (kQueryIndex) {
                     uint32_t sl, local;
                     divmod(qg, p.div_plane, sl, local);
                     s_el[m][1] = static_cast<int32_t>(local);
+                    one = p.causal && fabsf(lse) < INFINITY &&
+                          one_key_left(p, qg, local, static_cast<int>(mu), static_cast<int>(mv));
+                    lse = one ? 0.f : lse;
                 }
+                meta = make_int4(static_cast<int>(mu), static_cast<int>(mv), __float_as_int(lse), __float_as_int(dq));
                 if constexpr (MULTI) {
                     int32_t pc[kMaxKappa - 1];
 #pragma unroll
@@ -1329,6 +1359,14 @@ bwd_key_strip_f32_kernel(BwdParams p)
                 }
             }
             s_meta[m] = meta;
+        }
+        if constexpr (kQueryIndex) {
+            // a set of one key: its weight is 1 = 2^(0 - 0) and dS is 0 whatever order dP and D are summed in, so the
+            // query's row is left out of the products
+            uint32_t ones = static_cast<uint32_t>(__ballot(one));
+            if (ones != 0u) wave_lds_sync();  // after the rows' stores
+            for (; ones != 0u; ones &= ones - 1u)
+                if (lane < kLR) *reinterpret_cast<f32x4_t*>(s_q + __builtin_ctz(ones) * kRowF + 4 * lane) = zero;
         }
         code = next;
         if (c0 + kCE < E) fetch();
@@ -1926,7 +1964,7 @@ hipError_t run_backward(const BwdParams& p0, hipStream_t st, hipEvent_t* ev, Inv
     if ((e = inverse()) != hipSuccess) return e;
     // key side on the matrix cores; a one-key window (b = 0, or fp32 and a one-key grid) stays on the
     // lane-group kernels, whose dp is the query kernel's own arithmetic, so that dS = p (dp - D) is exactly
-    // 0 there
+    // 0 there (in fp32 also where the causal mask leaves a query one key: the strips set it)
     // (fp32 rows of 128 channels, whose fragments and sums overfill the registers, stay there too: two maps, 7 x 7,
     // 8 x 128 x 128 gained (2521 -> 1887 us), but 3 x 3 lost (569 -> 704) and so did small grids: 64 x 64 170 -> 291;
     // and several maps of 64 channels: 4 x 80 x 86 7 x 7 319 -> 266, 3 x 3 114 -> 122, 64 x 64 141 -> 161)

@@ -101,3 +101,29 @@ def test_non_finite_gradients_of_unions(scram, d, kappa, window, causal):
     rest = np.ones(d, bool)
     rest[[ch for ch, _ in bad.values()]] = False
     assert np.isfinite(dv[:, rest]).all()
+
+
+@pytest.mark.parametrize("grid", [(24, 24), (5, 70), (90, 1), (1, 90)], ids=lambda g: "x".join(map(str, g)))
+@pytest.mark.parametrize("d,kappa,window", [(16, 1, 3), (16, 3, 5), (32, 2, 3), (64, 1, 5), (64, 2, 3), (128, 1, 3)])
+def test_sets_of_one_key_leave_dK_alone(scram, d, kappa, window, grid):
+    """Where the causal mask leaves a query one key, its weight is 1 and dS is 0: the key's dK is exactly 0 and its dV
+    the query's dO, if no other query holds it."""
+    H, W = grid
+    S, b, rng = 8, window // 2, np.random.default_rng(d + kappa + H)
+    Q, K, V, dO = (to_dev(4 * rng.standard_normal((S, H, W, d)), "f32") for _ in range(4))
+    i = np.arange(H * W)
+    # windows that reach back to the query's own key and no further; the second map repeats it, the third holds no key
+    # that the mask keeps, except for the last queries
+    after = np.minimum(i // W + (b if H > 1 else 0), H - 1) * W + np.minimum(i % W + (b if W > 1 else 0), W - 1)
+    J = np.stack([after, after, np.full(H * W, H * W - 1)][:kappa]).astype(np.int32)
+    held = key_sets(J, H, W, window, True)
+    lone = held.sum(1) == 1
+    keys = np.flatnonzero((held[lone].sum(0) == 1) & (held[~lone].sum(0) == 0))
+    assert len(keys) > H * W // 8
+    owner = held[:, keys].argmax(0)
+    Jd = torch.from_numpy(np.broadcast_to(J.reshape(kappa, 1, H, W), (kappa, S, H, W)).copy()).cuda()
+    dQ, dK, dV = (x.cpu().reshape(S, H * W, d) for x in
+                  scram.sparse_attend_backward(Q, K, V, Jd, dO, window, causal=True))
+    assert not dK[:, keys].any()
+    assert torch.equal(dV[:, keys], dO.cpu().reshape(S, H * W, d)[:, owner])
+    assert not dQ[:, np.flatnonzero(lone)].any()
