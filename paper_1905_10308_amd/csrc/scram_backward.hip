@@ -2,6 +2,8 @@
 
 #include "scram_tile.h"
 
+#include <algorithm>
+
 namespace scram {
 namespace {
 
@@ -45,8 +47,9 @@ struct BwdParams {
     const int32_t* entries;  // [kappa * n] e * n + i, grouped by match key
     int32_t* counts;         // [S * nkeys] entries per match key (zeroed before the query kernel)
     int32_t* slots;          // [kappa * n] each entry's slot among its key's entries
-    int32_t* heavy;          // [S * nkeys] keys left to bwd_heavy_kernel
+    int32_t* heavy;          // [S * nkeys] keys left to bwd_heavy_kernel (fp32 strips: to bwd_strip_team_f32_kernel)
     int32_t* n_heavy;        // their count
+    int heavy_entries;       // fp32 strips: most entries of a strip that one wave sums
     void* qs;                // [kappa * n, D] q_i of each entry, in entry order
     void* gs;                // [kappa * n, D] dO_i of each entry, in entry order
     float2* st;              // [kappa * n] (log2 normaliser, D_i) of each entry
@@ -1430,10 +1433,15 @@ bwd_key_strip_f32_kernel(BwdParams p)
     constexpr int kOt = D / 16;
     __shared__ StripLds<D, MODE> lds;
     const int lane = threadIdx.x & 63;
-    const KeyStripF t(p.tk, xcd_remap(blockIdx.x, gridDim.x));
+    const uint32_t strip = xcd_remap(blockIdx.x, gridDim.x);
+    const KeyStripF t(p.tk, strip);
     if (t.sr0 >= p.Hk || t.sc0 >= p.Wk) return;  // the strip lies past the grid's edge
     int nrows;
     const int E = strip_entries(p, t, lds, lane, nrows);
+    if (E > p.heavy_entries) {
+        if (lane == 0) p.heavy[atomicAdd(p.n_heavy, 1)] = static_cast<int32_t>(strip);
+        return;
+    }
     f32x4_t dk[kOt], dv[kOt];
     strip_sums<D, MODE, false>(p, t, lds, lane, 0, 1, E, nrows, dk, dv);
     bool finite = true;
@@ -1456,6 +1464,68 @@ bwd_key_strip_f32_kernel(BwdParams p)
         for (int o = 0; o < kOt; ++o) ok[o] = dk[o][r] * p.scale, ov[o] = dv[o][r];
         store_floats<kOt>(p.dK + row, ok);
         store_floats<kOt>(p.dV + row, ov);
+    }
+}
+
+// The strips that the kernel above leaves, those of more than heavy_entries entries, whose one wave would run on when the
+// others are done: a team of kStripTeam waves each.  A team's waves take every kStripTeam-th chunk and their sums are
+// added through LDS.
+constexpr int kStripTeam = 8;
+constexpr uint32_t kTeamBlocks = 256;  // (one per CU: after 512, the next call's one-wave blocks of 1024 strips run 25 % longer)
+
+template <int D, int MODE>
+__global__ __launch_bounds__(64 * kStripTeam) __attribute__((amdgpu_waves_per_eu(D >= 32 ? 2 : 4))) void
+bwd_strip_team_f32_kernel(BwdParams p)
+{
+    constexpr int kOt = D / 16;
+    using Lds = StripLds<D, MODE>;
+    constexpr int kRowF = Lds::kRowF;
+    constexpr int kPieces = 16 * D / 4;  // of 4 floats, of the strip's dK and of its dV
+    __shared__ Lds lds[kStripTeam];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int m = lane & 15, g4 = lane >> 4;
+    const int count = *p.n_heavy;
+    for (int h = blockIdx.x; h < count; h += gridDim.x) {
+        const KeyStripF t(p.tk, static_cast<uint32_t>(p.heavy[h]));
+        int nrows;
+        const int E = strip_entries(p, t, lds[wave], lane, nrows);
+        f32x4_t dk[kOt], dv[kOt];
+        auto add_up = [&]() {  // whether all sums of the strip are finite
+            // this wave's sums over its staged rows: row i for key i
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                float ok[kOt], ov[kOt];
+#pragma unroll
+                for (int o = 0; o < kOt; ++o) ok[o] = dk[o][r], ov[o] = dv[o][r];
+                store_floats<kOt>(lds[wave].q + (4 * g4 + r) * kRowF + m * kOt, ok);
+                store_floats<kOt>(lds[wave].g + (4 * g4 + r) * kRowF + m * kOt, ov);
+            }
+            __syncthreads();
+            bool finite = true;
+            for (int x = threadIdx.x; x < 2 * kPieces; x += 64 * kStripTeam) {
+                const bool is_v = x >= kPieces;
+                const int i = (x & (kPieces - 1)) / (D / 4), c = 4 * (x & (D / 4 - 1));
+                f32x4_t sum = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int w = 0; w < kStripTeam; ++w)
+                    sum += *reinterpret_cast<const f32x4_t*>((is_v ? lds[w].g : lds[w].q) + i * kRowF + c);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) finite = finite && fabsf(sum[j]) < INFINITY;
+                int ox, oy;
+                t.key(i, ox, oy);
+                if (ox >= p.Hk || oy >= p.Wk) continue;
+                const size_t row = (static_cast<size_t>(t.s) * p.nkeys + static_cast<size_t>(ox) * p.Wk + oy) * D + c;
+                // (where the strip is summed again, by the same thread again)
+                *reinterpret_cast<f32x4_t*>((is_v ? p.dV : p.dK) + row) = is_v ? sum : sum * p.scale;
+            }
+            // (the sums are read before the next rows are staged)
+            return __syncthreads_or(!finite) == 0;
+        };
+        strip_sums<D, MODE, false>(p, t, lds[wave], lane, wave, kStripTeam, E, nrows, dk, dv);
+        if (!add_up()) {
+            strip_sums<D, MODE, true>(p, t, lds[wave], lane, wave, kStripTeam, E, nrows, dk, dv);
+            add_up();
+        }
     }
 }
 
@@ -1887,15 +1957,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))) voi
 #define SCRAM_BWD_QUERY_TILE 1
 #endif
 
-// launch() for kernels whose blocks are one wave each
+// launch() for kernels of another block size: one wave, by default
+template <uint32_t kThreads = 64>
 hipError_t launch_wave(void (*kernel)(BwdParams), uint64_t blocks, hipStream_t st, hipEvent_t start, hipEvent_t stop,
                        const BwdParams& p)
 {
-    if (blocks == 0 || blocks > 0xFFFFFFFFull / 64) return hipErrorInvalidConfiguration;
+    if (blocks == 0 || blocks > 0xFFFFFFFFull / kThreads) return hipErrorInvalidConfiguration;
     if (start || stop)
-        hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(64), 0, st, start, stop, 0, p);
+        hipExtLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, start, stop, 0, p);
     else
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(64), 0, st, p);
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kThreads), 0, st, p);
     return hipGetLastError();
 }
 
@@ -1970,8 +2041,23 @@ hipError_t run_backward(const BwdParams& p0, hipStream_t st, hipEvent_t* ev, Inv
         pt.tk = make_tiling(p.Hk, p.Wk, kTileKeys);
         const uint64_t tblocks = kStripWaves * tiling_blocks(pt.tk, p.keys_total / p.nkeys);
         if constexpr (std::is_same<T, float>::value) {
+            // One wave per strip up to the share of all strips' entries that each of 2048 waves would have (two per
+            // SIMD), or one and a half times a strip's mean if the teams of all strips are more waves than that; at
+            // least 8 chunks, one for each wave of a team.  1 x 128 x 128 keys, 64 channels, 3 x 3: all queries at
+            // one key 2514 us without teams, 621 with them, half of them at four keys 339 and 111 (the lane-group
+            // kernels, which share such keys among 8 groups: 805 and 144).  15 x 15, each query at its own key
+            // (mean 324): 141 without teams, 179 where the mean is not looked at.
+            const uint64_t halo = static_cast<uint64_t>(std::min(4 + 2 * p.b, p.Hk)) * std::min(4 + 2 * p.b, p.Wk);
+            const uint64_t all = static_cast<uint64_t>(p.n) * p.kappa * halo;  // 16 times the strips' entries
+            uint64_t most = std::max<uint64_t>(all / (16 * 2048), kStripTeam * kStripFE);
+            if (tblocks * kStripTeam > 2048) most = std::max<uint64_t>(most, 3 * all / (2 * static_cast<uint64_t>(p.keys_total)));
+            pt.heavy_entries = static_cast<int>(std::min<uint64_t>(most, INT32_MAX));
             auto go = [&](auto mode) {
-                return launch_wave(bwd_key_strip_f32_kernel<D, decltype(mode)::value>, tblocks, st, k0, k1, pt);
+                constexpr int MODE = decltype(mode)::value;
+                const hipError_t err = launch_wave(bwd_key_strip_f32_kernel<D, MODE>, tblocks, st, k0, nullptr, pt);
+                return err != hipSuccess ? err
+                                         : launch_wave<64 * kStripTeam>(bwd_strip_team_f32_kernel<D, MODE>, kTeamBlocks, st,
+                                                                      nullptr, k1, pt);
             };
             if constexpr (D < 64)
                 if (p.kappa > 1) return go(std::integral_constant<int, kStripMulti>{});

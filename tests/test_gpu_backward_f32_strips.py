@@ -129,6 +129,27 @@ def test_sets_of_one_key_leave_dK_alone(scram, d, kappa, window, grid):
     assert not dQ[:, np.flatnonzero(lone)].any()
 
 
+@pytest.mark.parametrize("d,kappa,window", [(16, 1, 3), (16, 2, 5), (32, 1, 7), (32, 3, 3), (64, 1, 3), (64, 1, 15)])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("many", [128, 129, 1025, 2200])
+def test_strips_that_a_team_sums(scram, d, kappa, window, causal, many):
+    """Keys that many queries share, by one wave up to 128 entries of a strip and by 8 waves above: one entry more,
+    more than eight chunks for each of the waves, a remainder."""
+    H = W = 48
+    rng = np.random.default_rng(many + d)
+    Q, K, V, dO = (rng.standard_normal((1, H, W, d)).astype(np.float32) for _ in range(4))
+    q = np.arange(H * W)
+    # the other queries at the grid's end
+    J = np.stack([np.where(q < many, (5 + 9 * c) * W + 6, H * W - 1 - q % 200) for c in range(kappa)])
+    J = J.reshape(kappa, 1, H, W).astype(np.int32)
+    dev = [to_dev(x, "f32") for x in (Q, K, V)]
+    got = scram.sparse_attend_backward(*dev, torch.from_numpy(J).cuda(), to_dev(dO, "f32"), window, causal=causal)
+    ref = oracle.sparse_attend_backward(Q, K, V, J, window, d ** -0.5, dO, flags=oracle.CAUSAL if causal else 0)
+    for name, g, r in zip(("dQ", "dK", "dV"), got, ref):
+        err = np.abs(g.double().cpu().numpy() - r).max() / np.abs(r).max()
+        assert err <= 2e-5, (name, err)  # the bar of the other backward tests
+
+
 def _us(fn, n=10):
     for _ in range(3):
         fn()
@@ -144,13 +165,17 @@ def _us(fn, n=10):
     return best
 
 
-def test_time_of_rows_that_are_not_finite(scram):
-    """One NaN in dO against finite rows: 1.7 times the time; 10 times where the keys of a strip that is not finite are
-    summed one by one."""
+def test_time_of_shared_keys_and_of_rows_that_are_not_finite(scram):
+    """A map that takes all queries to one key, and one NaN in dO, against the queries' own keys and finite rows.
+    Measured: 18 and 1.7 times the time; 80 and 10 where one wave sums all entries of a strip and where the keys of a
+    strip that is not finite are summed one by one."""
     H, d = 128, 64
     gen = torch.Generator(device="cuda").manual_seed(5)
     Q, K, V, dO = (torch.randn(1, H, H, d, device="cuda", generator=gen) for _ in range(4))
     own = torch.arange(H * H, dtype=torch.int32, device="cuda").reshape(1, H, H)
+    one = torch.full_like(own, H * H // 2 + H // 2)
+    base = _us(lambda: scram.sparse_attend_backward(Q, K, V, own, dO, 3))
+    assert _us(lambda: scram.sparse_attend_backward(Q, K, V, one, dO, 3)) < 45 * base
     base = _us(lambda: scram.sparse_attend_backward(Q, K, V, own, dO, 7))
     dO[0, H // 2, H // 2, 1] = float("nan")
     assert _us(lambda: scram.sparse_attend_backward(Q, K, V, own, dO, 7)) < 4 * base
