@@ -857,8 +857,10 @@ hipError_t run_attend_m(const AttParams& p, int window, uint64_t blocks, hipStre
 // 25 -> 30).  The others gain where matches lie together (PatchMatch maps of
 // smooth images, 8 x 97 x 111: 128 channels 7 x 7 85 -> 50 us, two 5 x 5
 // windows 98 -> 64, two 9 x 9 251 -> 93; 16 channels 7 x 7 29 -> 22; 64
-// channels 9 x 9 74 -> 38), and keep the lane groups' time where they do not:
-// there a wave leaves the matrix cores (tile_blocks).  With 128 channels that
+// channels 9 x 9 74 -> 38); where they do not, a wave leaves the matrix cores
+// (tile_blocks) and a call takes 0.7 to 1.4 of the lane groups' time (random
+// matches, 16 channels 7 x 7 40 -> 29, three causal 9 x 9 windows of 64
+// channels 222 -> 279).  With 128 channels that
 // way takes a wave two rounds of 8 queries, which only a call that fills the
 // machine hides (two 5 x 5 windows, maps of noise: 4 x 64 x 64, one wave per
 // SIMD, 1.4 times the lane groups' time, 8 x 64 x 64 1.06), so smaller calls
