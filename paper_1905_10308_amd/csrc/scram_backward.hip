@@ -1471,7 +1471,11 @@ bwd_key_strip_f32_kernel(BwdParams p)
 // others are done: a team of kStripTeam waves each.  A team's waves take every kStripTeam-th chunk and their sums are
 // added through LDS.
 constexpr int kStripTeam = 8;
-constexpr uint32_t kTeamBlocks = 256;  // (one per CU: after 512, the next call's one-wave blocks of 1024 strips run 25 % longer)
+// As many blocks as are resident, one per CU (16 channels: two).  With 512 at 32 and 64 channels the one-wave blocks of the
+// next call's 1024 strips ran 25 % longer; 256 at 16 channels, two 7 x 7 maps that lie in a 16th of the grid,
+// 32 x 64 x 64: 356 us, 512: 314.
+template <int D>
+constexpr uint32_t kTeamBlocks = D >= 32 ? 256 : 512;
 
 template <int D, int MODE>
 __global__ __launch_bounds__(64 * kStripTeam) __attribute__((amdgpu_waves_per_eu(D >= 32 ? 2 : 4))) void
@@ -2056,7 +2060,7 @@ hipError_t run_backward(const BwdParams& p0, hipStream_t st, hipEvent_t* ev, Inv
                 constexpr int MODE = decltype(mode)::value;
                 const hipError_t err = launch_wave(bwd_key_strip_f32_kernel<D, MODE>, tblocks, st, k0, nullptr, pt);
                 return err != hipSuccess ? err
-                                         : launch_wave<64 * kStripTeam>(bwd_strip_team_f32_kernel<D, MODE>, kTeamBlocks, st,
+                                         : launch_wave<64 * kStripTeam>(bwd_strip_team_f32_kernel<D, MODE>, kTeamBlocks<D>, st,
                                                                       nullptr, k1, pt);
             };
             if constexpr (D < 64)
